@@ -202,12 +202,12 @@ struct CellArgs {
 };
 
 // Suspension-wide sums (lbm_get_stats): node pass over the lattice rows with a
-// fixed number of workgroups, one row of STATS_PK values per particle, one
-// final workgroup.  tot receives 4 + STATS_PK values: mass, j (3), then the
+// fixed number of workgroups, one column of np values per particle quantity,
+// one final workgroup per total.  tot receives 4 + STATS_PK values: mass, j (3), then the
 // particle sums m v (3), v (3), F^h (3), eps-share of mass, of momentum (3),
 // eps (the node's solid fraction split over its owners), m.
 constexpr int STATS_NT = 256;
-constexpr int STATS_NODE_GROUPS = 1024;
+constexpr int STATS_NODE_GROUPS = 2048;
 constexpr int STATS_PK = 15;
 
 struct StatsArgs {
@@ -218,7 +218,7 @@ struct StatsArgs {
     int rec32;
     int Smax;
     double *node_part;     // [STATS_NODE_GROUPS][4]
-    double *part_rows;     // [np][STATS_PK]
+    double *part_cols;     // [STATS_PK][np]
     double *tot;           // [4 + STATS_PK]
 };
 

@@ -115,7 +115,7 @@ Layout make_layout(const lbm_config *c) {
     L.off_cid = take((size_t)L.cell_budget * CELL_CAP * 4);
     L.off_flags = take(64);
     L.off_tab = take((size_t)EPS_TAB_NRHO * EPS_TAB_NT * EPS_TAB_NT * 2);
-    // lbm_get_stats: node-pass partials, one row per particle, the totals
+    // lbm_get_stats: node-pass partials, the particle columns, the totals
     L.off_stats = take(((size_t)STATS_NODE_GROUPS * 4 + P * STATS_PK + 4 + STATS_PK) * 8);
     // neighbour-list mode: lists, build positions, guard state and build count
     L.off_nl = take(P * NL_CAP * 4);
@@ -1434,8 +1434,8 @@ int lbm_get_stats(lbm_ctx *c, lbm_stats *out) {
     a.Smax = c->L.Smax;
     double *base = wsp<double>(c, c->L.off_stats);
     a.node_part = base;
-    a.part_rows = base + (size_t)STATS_NODE_GROUPS * 4;
-    a.tot = a.part_rows + (size_t)c->L.P * STATS_PK;
+    a.part_cols = base + (size_t)STATS_NODE_GROUPS * 4;
+    a.tot = a.part_cols + (size_t)c->L.P * STATS_PK;
     HIPCHK(c, launch_stats(c->cfg.lattice, c->cfg.storage, a, c->stream));
     double s[4 + STATS_PK];
     HIPCHK(c, hipMemcpyAsync(s, a.tot, sizeof(s), hipMemcpyDeviceToHost, c->stream));
