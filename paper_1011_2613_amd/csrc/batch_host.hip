@@ -26,7 +26,7 @@ struct BLayout {
     int nbox, nsph, Smax, ntiles;
     int64_t total_nodes, pool, list_total;
     size_t A, B, cnt, q, beta, arel, boxes, tile_box, queue, done, flags, sph_box, sph_x, lstart, list, F,
-        T, U, Fprev, steady, stop, misc, Us, feat, total;
+        T, U, Upart, Fprev, steady, stop, misc, Us, feat, total;
 };
 
 double pdisp(double d, double L) {
@@ -111,6 +111,7 @@ BLayout make_blayout(const lbm_box *boxes, int nbox, int S, int64_t list_total) 
     L.F = take((size_t)std::max(nsph, 1) * 24);
     L.T = take((size_t)std::max(nsph, 1) * 24);
     L.U = take((size_t)nbox * 24);
+    L.Upart = take((size_t)nbox * BATCH_MEAN_PARTS * 24);
     L.Fprev = take((size_t)std::max(nsph, 1) * 24);
     L.steady = take((size_t)nbox * 4);
     L.stop = take((size_t)nbox * 8);
@@ -505,7 +506,7 @@ int lbm_batch_forces(lbm_batch *c, double *F, double *T, int ptr_kind) {
 
 int lbm_batch_mean_velocity(lbm_batch *c, double *U, int ptr_kind) {
     if (!c || !U) return LBM_E_INVALID;
-    if (launch_batch_mean(bargs(c), c->cur, Pp<double>(c, c->L.U), c->s) != hipSuccess) return LBM_E_HIP;
+    if (launch_batch_mean(bargs(c), c->cur, Pp<double>(c, c->L.Upart), Pp<double>(c, c->L.U), c->s) != hipSuccess) return LBM_E_HIP;
     const hipMemcpyKind k = ptr_kind == LBM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
     if (hipMemcpyAsync(U, c->ws + c->L.U, (size_t)c->L.nbox * 24, k, c->s) != hipSuccess) return LBM_E_HIP;
     return hipStreamSynchronize(c->s) == hipSuccess ? LBM_OK : LBM_E_HIP;
@@ -602,7 +603,7 @@ int lbm_batch_get_drag(lbm_batch *c, double *F, float *feat, int ptr_kind) {
         BatchArgs a = bargs(c);
         double *U = Pp<double>(c, c->L.U), *Us = Pp<double>(c, c->L.Us);
         float *X = Pp<float>(c, c->L.feat);
-        hipError_t e = launch_batch_mean(a, c->cur, U, c->s);
+        hipError_t e = launch_batch_mean(a, c->cur, Pp<double>(c, c->L.Upart), U, c->s);
         if (e == hipSuccess) e = launch_batch_shell(a, c->cur, Us, c->s);
         if (e == hipSuccess) e = launch_batch_features(a, U, Us, X, c->s);
         if (e == hipSuccess) e = hipMemcpyAsync(feat, X, (size_t)nsph * 160, k, c->s);

@@ -252,6 +252,8 @@ struct BatchSteady {
     double tol;
 };
 
+constexpr int BATCH_MEAN_PARTS = 128;  // workgroups per box of the mean-velocity sums
+
 struct BatchArgs {
     float *A, *B;              // population pool, shifted storage
     const BatchBox *boxes;
@@ -277,7 +279,7 @@ struct BatchArgs {
 hipError_t launch_batch_step(const BatchArgs &a, int parity, hipStream_t s);
 hipError_t launch_batch_persistent(const BatchArgs &a, int nsteps, int parity0, int grid, hipStream_t s);
 hipError_t launch_batch_force(const BatchArgs &a, hipStream_t s);
-hipError_t launch_batch_mean(const BatchArgs &a, int parity, double *U, hipStream_t s);
+hipError_t launch_batch_mean(const BatchArgs &a, int parity, double *part, double *U, hipStream_t s);
 hipError_t launch_batch_get_f(const BatchArgs &a, int b, int L, int parity, double *f, hipStream_t s);
 hipError_t launch_batch_init(const BatchArgs &a, int nbox, int maxL, hipStream_t s);
 hipError_t launch_batch_shell(const BatchArgs &a, int parity, double *u, hipStream_t s);
