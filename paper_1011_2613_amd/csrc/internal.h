@@ -62,10 +62,26 @@ struct Particles {
     double *Fh, *Th, *Fc;  // hydrodynamic force/torque, contact force
     int *bb;               // [6][P] painted bounding box, lower and upper corner
     uint32_t *list;        // [P][list_cap] covered nodes: count | kx << 10 | ky << 17 | kz << 24
-    int *list_len;         // [P]
+    int *list_len;         // [np][nseg]
     int list_cap;
+    int nseg;              // segments of each list: segment s starts at entry s list_seg()
     int np;
 };
+
+// Footprint segments per particle (foot_segments): at most FOOT_SEG_MAX, and
+// np nseg below FOOT_SEG_UNITS where there is more than one.
+constexpr int FOOT_SEG_MAX = 256;
+constexpr int FOOT_SEG_UNITS = 4096;
+int foot_segments(int D, int np, double rmax);
+
+// Entries between the starts of two segments of particle p's list: its
+// bounding box's items split evenly.
+__device__ __forceinline__ int list_seg(const Particles &P, int p) {
+    const int np = P.np;
+    const int items = (P.bb[3 * np + p] - P.bb[p] + 1) * (P.bb[4 * np + p] - P.bb[np + p] + 1) *
+                      (P.bb[5 * np + p] - P.bb[2 * np + p] + 1);
+    return (items + P.nseg - 1) / P.nseg;
+}
 
 // Lattice geometry shared by every kernel.
 struct Geom {
@@ -175,6 +191,7 @@ struct ForceArgs {
     int D;
     int integrate;         // 1: the kernel also advances the particle (needs F^c of this step)
     double ap[3];          // particle acceleration (gravity with buoyancy)
+    int entries;           // list entries of the largest particle, about
     uint32_t *flags;
     Groups G;              // G.K > 1: the integration also files the particle in its next group
 };

@@ -107,7 +107,7 @@ Layout make_layout(const lbm_config *c) {
         const size_t o0 = o;
         L.off_bb = take(6 * P * 4);
         L.off_list = take(P * (size_t)L.list_cap * 4);
-        L.off_list_len = take(P * 4);
+        L.off_list_len = take(std::max<size_t>(P, FOOT_SEG_UNITS) * 4);
         L.list_buf = o - o0;
         o += L.list_buf;
     }
@@ -167,6 +167,7 @@ struct lbm_ctx {
     int nl_every;      // 0: cell list every step; else neighbour lists, rebuilt after nl_every steps at most
     double nl_skin;    // list margin beyond contact
     double prmax;      // largest radius of the current particles
+    int nseg[2];       // segments per list of the two footprint buffers
     bool rec_open;
     std::vector<TimedEvent> events;
     size_t ev_used;
@@ -216,6 +217,7 @@ Particles particles(lbm_ctx *c, int buf) {
     P.list = wsp<uint32_t>(c, c->L.off_list + fb);
     P.list_len = wsp<int>(c, c->L.off_list_len + fb);
     P.list_cap = c->L.list_cap;
+    P.nseg = c->nseg[buf];
     P.np = c->np;
     return P;
 }
@@ -357,6 +359,9 @@ hipError_t pipe_setup(lbm_ctx *c) {
 FootArgs foot_args(lbm_ctx *c, int buf, const Groups &G) {
     FootArgs a;
     a.G = G;
+    // the table lookup and the slab pipeline keep one segment per particle
+    const bool plain = c->cfg.eps_mode == LBM_EPS_SAMPLING && c->pipe_K == 1;
+    c->nseg[buf] = plain ? foot_segments(c->L.D, c->np, c->prmax) : 1;
     a.P = particles(c, buf);
     a.g = c->g;
     a.nown = wsp<uint8_t>(c, c->L.off_nown);
@@ -464,6 +469,7 @@ ForceArgs force_args(lbm_ctx *c, int buf, const Groups &G) {
     fo.D = c->L.D;
     fo.integrate = 1;
     for (int d = 0; d < 3; d++) fo.ap[d] = c->cfg.particle_accel[d];
+    fo.entries = (int)(c->L.D == 2 ? M_PI * c->prmax * c->prmax : 4.0 / 3.0 * M_PI * std::pow(c->prmax, 3));
     fo.flags = flags(c);
     fo.G = G;
     return fo;
@@ -776,6 +782,7 @@ int lbm_create(const lbm_config *cfg, void *workspace, size_t ws_bytes, void *hi
     c->nl_every = 0;
     c->nl_skin = 1.0;
     c->prmax = 0.0;
+    c->nseg[0] = c->nseg[1] = 1;
     c->pipe_req = 1;  // off: measured slower than the plain step on MI355X
     c->pipe_K = 1;
     c->rec_open = false;
@@ -973,9 +980,11 @@ int lbm_set_particles(lbm_ctx *c, int64_t n, const double *pos, const double *ve
     HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_Fh), 0u, (int64_t)(3 * np * 2), c->stream));
     HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_Th), 0u, (int64_t)(3 * np * 2), c->stream));
     HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_Fc), 0u, (int64_t)(3 * np * 2), c->stream));
-    for (int b = 0; b < 2; b++)
+    for (int b = 0; b < 2; b++) {
+        c->nseg[b] = 1;
         HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_list_len + (size_t)b * c->L.list_buf), 0u,
                                   (int64_t)np, c->stream));
+    }
     // a new particle set starts with clear health flags
     HIPCHK(c, launch_fill_u32(flags(c), 0u, 16, c->stream));
     c->particles_set = true;
@@ -1412,9 +1421,11 @@ int lbm_load(lbm_ctx *c, const char *path) {
     c->t = t;
     c->particles_set = true;
     HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_nown), 0u, (int64_t)((c->L.N + 7) / 8 * 2), c->stream));
-    for (int b = 0; b < 2; b++)
+    for (int b = 0; b < 2; b++) {
+        c->nseg[b] = 1;
         HIPCHK(c, launch_fill_u32(wsp<uint32_t>(c, c->L.off_list_len + (size_t)b * c->L.list_buf), 0u,
                                   (int64_t)P, c->stream));
+    }
     HIPCHK(c, launch_fill_u32(flags(c), 0u, 16, c->stream));
     c->pipe_K = 1;  // the footprint is forgotten: set the pipeline up afresh
     HIPCHK(c, pipe_setup(c));

@@ -142,26 +142,32 @@ __global__ __launch_bounds__(NT) void k_stats_particles(const void *A, Geom g, P
     const int p = blockIdx.x;
     const int np = P.np;
     double w5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // rho, j and eps shares
-    const int len = P.list_len[p];
     const int lo0 = P.bb[p], lo1 = P.bb[np + p], lo2 = P.bb[2 * np + p];
-    const uint32_t *list = P.list + (int64_t)p * P.list_cap;
-    for (int e = threadIdx.x; e < len; e += NT) {
-        const uint32_t v = list[e];
-        const int x = wrap_list(g, 0, lo0 + (int)((v >> 10) & 127u));
-        const int y = g.wall_y ? lo1 + (int)((v >> 17) & 127u) : wrap_list(g, 1, lo1 + (int)((v >> 17) & 127u));
-        const int z = L::D == 3 ? wrap_list(g, 2, lo2 + (int)((v >> 24) & 127u)) : 0;
-        const int64_t n = (int64_t)x + (int64_t)g.nx * ((int64_t)y + (int64_t)g.ny * z);
-        double q[3];
-        int tot;
-        read_qrec(qr, rec32 != 0, n, q, tot);
-        const int cnt = (int)(v & 1023u);
-        const double eps = (double)(tot < Smax ? tot : Smax) / (double)Smax;
-        const double w = ((double)cnt / (double)tot) * eps;
-        double rho, j[3];
-        node_moments<L, ST>(A, g, x, y, z, rho, j);
-        w5[0] = w5[0] + w * rho;
-        for (int d = 0; d < 3; d++) w5[1 + d] = w5[1 + d] + w * j[d];
-        w5[4] = w5[4] + w;
+    const int seg = P.nseg > 1 ? list_seg(P, p) : 0;
+    // thread t takes the list's entries t, t + NT, ... whatever the segments
+    int before = 0;
+    for (int sg = 0; sg < P.nseg; sg++) {
+        const uint32_t *list = P.list + (int64_t)p * P.list_cap + sg * seg;
+        const int len = P.list_len[(int64_t)p * P.nseg + sg];
+        for (int e = ((int)threadIdx.x - before) & (NT - 1); e < len; e += NT) {
+            const uint32_t v = list[e];
+            const int x = wrap_list(g, 0, lo0 + (int)((v >> 10) & 127u));
+            const int y = g.wall_y ? lo1 + (int)((v >> 17) & 127u) : wrap_list(g, 1, lo1 + (int)((v >> 17) & 127u));
+            const int z = L::D == 3 ? wrap_list(g, 2, lo2 + (int)((v >> 24) & 127u)) : 0;
+            const int64_t n = (int64_t)x + (int64_t)g.nx * ((int64_t)y + (int64_t)g.ny * z);
+            double q[3];
+            int tot;
+            read_qrec(qr, rec32 != 0, n, q, tot);
+            const int cnt = (int)(v & 1023u);
+            const double eps = (double)(tot < Smax ? tot : Smax) / (double)Smax;
+            const double w = ((double)cnt / (double)tot) * eps;
+            double rho, j[3];
+            node_moments<L, ST>(A, g, x, y, z, rho, j);
+            w5[0] = w5[0] + w * rho;
+            for (int d = 0; d < 3; d++) w5[1 + d] = w5[1 + d] + w * j[d];
+            w5[4] = w5[4] + w;
+        }
+        before += len;
     }
     __shared__ double s[NT / 64][5];
 #pragma unroll
