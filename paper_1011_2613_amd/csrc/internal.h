@@ -192,6 +192,9 @@ struct ForceArgs {
     int integrate;         // 1: the kernel also advances the particle (needs F^c of this step)
     double ap[3];          // particle acceleration (gravity with buoyancy)
     int entries;           // list entries of the largest particle, about
+    int file;              // 1: file the particle in the next step's cell list too
+    int nc[3];             // cells per axis
+    int *cell_old, *cell_new, *cell_ids;  // counts of this and the next step's list
     uint32_t *flags;
     Groups G;              // G.K > 1: the integration also files the particle in its next group
 };
@@ -331,6 +334,9 @@ hipError_t launch_stats(int lattice, int storage, const StatsArgs &a, hipStream_
 
 // launchers (particle_kernels.hip)
 hipError_t launch_foot_paint(const FootArgs &a, int D, hipStream_t s);
+// footprints and the contacts of the step from its cell list, in one launch
+// (plain step, sampled eps)
+hipError_t launch_foot_dem(const FootArgs &a, const CellArgs &c, int D, hipStream_t s);
 hipError_t launch_force(const ForceArgs &a, hipStream_t s);
 // files every particle in its group of the current step (G.nlist / G.ncount
 // must be cleared first)

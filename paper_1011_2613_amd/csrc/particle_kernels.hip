@@ -350,12 +350,222 @@ __device__ __forceinline__ void foot_one(const FootArgs &a, int p) {
     }
 }
 
-// LDS written by some lanes of a wavefront and read by others, in a kernel
-// of one wavefront per workgroup: order the accesses within the wavefront.
+// LDS written by some lanes of a wavefront and read by others of the same
+// wavefront: order the accesses within it.
 __device__ __forceinline__ void lane_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ------------------------------------------------------------- cell list
+__device__ __forceinline__ int cell_coord(const Geom &g, int nc, int axis, double x) {
+    const double L = axis == 0 ? g.Lx : (axis == 1 ? g.Ly : g.Lz);
+    double t = x;
+    if (axis == 1 && g.wall_y) t = x + 0.5;
+    int c = (int)floor(t * (double)nc / L);
+    return c < 0 ? 0 : (c >= nc ? nc - 1 : c);
+}
+
+__device__ __forceinline__ int cell_coord(const CellArgs &a, int axis, double x) {
+    return cell_coord(a.g, axis == 0 ? a.ncx : (axis == 1 ? a.ncy : a.ncz), axis, x);
+}
+
+__device__ __forceinline__ void file_in_cell(int *cell_count, int *cell_ids, uint32_t *flags, int c, int p) {
+    const int slot = atomicAdd(&cell_count[c], 1);
+    if (slot < CELL_CAP) cell_ids[c * CELL_CAP + slot] = p;
+    else atomicOr(flags, FLAG_CELL_OVERFLOW);
+}
+
+__global__ void k_cells(CellArgs a) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int P = a.P.np;
+    if (p >= P) return;
+    const int cx = cell_coord(a, 0, a.P.x[p]);
+    const int cy = cell_coord(a, 1, a.P.x[P + p]);
+    const int cz = a.D == 3 ? cell_coord(a, 2, a.P.x[2 * P + p]) : 0;
+    file_in_cell(a.cell_count, a.cell_ids, a.flags, cx + a.ncx * (cy + a.ncy * cz), p);
+}
+
+// Neighbour cell offsets along one axis: {-1,0,1} wrapped (periodic, >= 3
+// cells), {0,1} (2 cells), {0} (1 cell), or {-1,0,1} clipped at walls.
+__device__ __forceinline__ int axis_cells(int c, int nc, bool periodic, int out[3]) {
+    if (periodic) {
+        if (nc >= 3) { out[0] = c == 0 ? nc - 1 : c - 1; out[1] = c; out[2] = c == nc - 1 ? 0 : c + 1; return 3; }
+        if (nc == 2) { out[0] = 0; out[1] = 1; return 2; }
+        out[0] = 0;
+        return 1;
+    }
+    int k = 0;
+    for (int d = -1; d <= 1; d++)
+        if (c + d >= 0 && c + d < nc) out[k++] = c + d;
+    return k;
+}
+
+// Contact test and force of Eqs. 4-5 for the pair (i, j) with the overlap
+// delta = R_i + R_j - |r_i - r_j| (minimum image).  Returns false when the
+// particles do not touch.
+__device__ __forceinline__ bool pair_force(const CellArgs &a, int i, int j, double F[3]) {
+    const int P = a.P.np, D = a.D;
+    double d[3] = {0.0, 0.0, 0.0};
+    for (int ax = 0; ax < D; ax++) {
+        double dd = a.P.x[ax * P + i] - a.P.x[ax * P + j];
+        if (!(ax == 1 && a.g.wall_y)) dd = pdisp(dd, ax == 0 ? a.g.Lx : (ax == 1 ? a.g.Ly : a.g.Lz));
+        d[ax] = dd;
+    }
+    double d2 = d[0] * d[0] + d[1] * d[1];
+    if (D == 3) d2 = d2 + d[2] * d[2];
+    const double dist = sqrt(d2);
+    const double delta = (a.P.R[i] + a.P.R[j]) - dist;
+    if (!(delta > 0.0)) return false;
+    if (F) {
+        double nrm[3] = {0.0, 0.0, 0.0};
+        for (int ax = 0; ax < D; ax++) nrm[ax] = d[ax] / dist;
+        double vn = (a.P.v[i] - a.P.v[j]) * nrm[0] + (a.P.v[P + i] - a.P.v[P + j]) * nrm[1];
+        if (D == 3) vn = vn + (a.P.v[2 * P + i] - a.P.v[2 * P + j]) * nrm[2];
+        const double meff = a.P.m[i] * a.P.m[j] / (a.P.m[i] + a.P.m[j]);
+        const double eta = a.ce * sqrt(meff * a.kn);
+        const double fmag = a.kn * delta - eta * vn;
+        for (int ax = 0; ax < D; ax++) F[ax] = F[ax] + fmag * nrm[ax];
+    }
+    return true;
+}
+
+// Wall contacts of particle i (Eqs. 4-5 against a wall at rest, m_eff = m_i),
+// added to F after the pair forces.
+__device__ __forceinline__ void wall_force(const CellArgs &a, int i, double F[3]) {
+    if (!a.g.wall_y) return;
+    const int P = a.P.np;
+    const double eta = a.ce * sqrt(a.P.m[i] * a.kn);
+    const double y = a.P.x[P + i];
+    const double vy = a.P.v[P + i];
+    const double dl = a.P.R[i] - (y + 0.5);
+    if (dl > 0.0) {
+        const double fmag = a.kn * dl - eta * vy;
+        F[1] = F[1] + fmag;
+    }
+    const double du = a.P.R[i] - ((a.g.Ly - 0.5) - y);
+    if (du > 0.0) {
+        const double fmag = a.kn * du - eta * (-vy);
+        F[1] = F[1] - fmag;
+    }
+}
+
+// Contacts of particle i by one wavefront: each lane scans one neighbour cell,
+// touching neighbours are gathered in LDS (`list`, `nl`: this wavefront's own),
+// sorted by id, and the pair forces are added in ascending id (then the walls)
+// by the first lane.
+__device__ __forceinline__ void dem_wave(const CellArgs &a, int i, int *list, int *nl) {
+    const int lane = threadIdx.x & 63;
+    const int P = a.P.np;
+    const int D = a.D;
+    if (lane == 0) *nl = 0;
+    lane_sync();
+    if (i < P) {
+        const int c0 = cell_coord(a, 0, a.P.x[i]);
+        const int c1 = cell_coord(a, 1, a.P.x[P + i]);
+        const int c2 = D == 3 ? cell_coord(a, 2, a.P.x[2 * P + i]) : 0;
+        int ox[3], oy[3], oz[3];
+        const int nxc = axis_cells(c0, a.ncx, true, ox);
+        const int nyc = axis_cells(c1, a.ncy, !a.g.wall_y, oy);
+        int nzc = 1;
+        oz[0] = 0;
+        if (D == 3) nzc = axis_cells(c2, a.ncz, true, oz);
+        if (lane < nxc * nyc * nzc) {
+            const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
+            const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
+            const int cnt = min(a.cell_count[c], CELL_CAP);
+            for (int s = 0; s < cnt; s++) {
+                const int j = a.cell_ids[c * CELL_CAP + s];
+                if (j == i) continue;
+                if (!pair_force(a, i, j, nullptr)) continue;
+                const int slot = atomicAdd(nl, 1);
+                if (slot < MAX_CONTACTS) list[slot] = j;
+                else atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
+            }
+        }
+    }
+    lane_sync();
+    if (i < P && lane == 0) {
+        const int n = min(*nl, MAX_CONTACTS);
+        for (int s = 1; s < n; s++) {
+            const int v = list[s];
+            int t = s - 1;
+            while (t >= 0 && list[t] > v) {
+                list[t + 1] = list[t];
+                t--;
+            }
+            list[t + 1] = v;
+        }
+        double F[3] = {0.0, 0.0, 0.0};
+        for (int s = 0; s < n; s++) pair_force(a, i, list[s], F);
+        wall_force(a, i, F);
+        for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_dem(CellArgs a) {
+    __shared__ int list[4][MAX_CONTACTS];
+    __shared__ int nlist[4];
+    const int wave = threadIdx.x >> 6;
+    dem_wave(a, (int)blockIdx.x * 4 + wave, list[wave], &nlist[wave]);
+}
+
+// Contacts of particle i by one thread, for many particles (dem_wave keeps a
+// wavefront busy with 9 or 27 neighbour cells, most of its lanes idle in 2D): the thread
+// walks the neighbour cells itself and inserts each touching neighbour into
+// its own id-sorted column of LDS, then adds the pair forces in ascending id
+// and the walls, the sum order of k_dem, so both kernels give the same bits.
+template <int NT>
+__device__ __forceinline__ void dem_thread(const CellArgs &a, int i, int (*list)[NT]) {
+    const int t = threadIdx.x;
+    const int P = a.P.np;
+    const int D = a.D;
+    if (i >= P) return;  // no barrier below
+    const int c0 = cell_coord(a, 0, a.P.x[i]);
+    const int c1 = cell_coord(a, 1, a.P.x[P + i]);
+    const int c2 = D == 3 ? cell_coord(a, 2, a.P.x[2 * P + i]) : 0;
+    int ox[3], oy[3], oz[3];
+    const int nxc = axis_cells(c0, a.ncx, true, ox);
+    const int nyc = axis_cells(c1, a.ncy, !a.g.wall_y, oy);
+    int nzc = 1;
+    oz[0] = 0;
+    if (D == 3) nzc = axis_cells(c2, a.ncz, true, oz);
+    int nl = 0;
+    bool overflow = false;
+    for (int kz = 0; kz < nzc; kz++)
+        for (int ky = 0; ky < nyc; ky++)
+            for (int kx = 0; kx < nxc; kx++) {
+                const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
+                const int cnt = min(a.cell_count[c], CELL_CAP);
+                for (int s = 0; s < cnt; s++) {
+                    const int j = a.cell_ids[c * CELL_CAP + s];
+                    if (j == i) continue;
+                    if (!pair_force(a, i, j, nullptr)) continue;
+                    if (nl >= MAX_CONTACTS) {
+                        overflow = true;
+                        continue;
+                    }
+                    int q = nl;
+                    while (q > 0 && list[q - 1][t] > j) {
+                        list[q][t] = list[q - 1][t];
+                        q--;
+                    }
+                    list[q][t] = j;
+                    nl++;
+                }
+            }
+    if (overflow) atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
+    double F[3] = {0.0, 0.0, 0.0};
+    for (int s = 0; s < nl; s++) pair_force(a, i, list[s][t], F);
+    wall_force(a, i, F);
+    for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_dem_thread(CellArgs a) {
+    __shared__ int list[MAX_CONTACTS][NT];
+    dem_thread<NT>(a, (int)blockIdx.x * NT + (int)threadIdx.x, list);
 }
 
 // Footprints on the plain step.  LPP lanes of a wavefront (one wavefront per
@@ -383,14 +593,21 @@ __device__ __forceinline__ void lane_sync() {
 // 155 against 224 us, 21 361 discs R = 5 37 against 43 us; with segments 310
 // spheres R = 5.3 11 against 44 us, 16 discs R = 6 5.4 against 22.6 us, one
 // sphere R = 16 6.7 against 784 us.
+template <int D, int LPP>
+struct FootLds {
+    static constexpr int G = 64 / LPP, CHUNK = D == 3 ? 1024 : 512;
+    uint32_t ent[G][CHUNK];  // list entries; count 0: not covered
+    uint16_t todo[G][CHUNK];
+};
+
 template <int D, int S, int LPP>
-__global__ __launch_bounds__(64) void k_foot(FootArgs a) {
-    constexpr int G = 64 / LPP, CHUNK = D == 3 ? 1024 : 512;
-    __shared__ uint32_t s_ent[G][CHUNK];  // list entries; count 0: not covered
-    __shared__ uint16_t s_todo[G][CHUNK];
+__device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootLds<D, LPP> &lds) {
+    constexpr int G = 64 / LPP, CHUNK = FootLds<D, LPP>::CHUNK;
+    uint32_t(&s_ent)[G][CHUNK] = lds.ent;
+    uint16_t(&s_todo)[G][CHUNK] = lds.todo;
     const int lane = (int)threadIdx.x, grp = lane / LPP, sub = lane % LPP;
     const int P = a.P.np, nseg = LPP == 64 ? a.P.nseg : 1;
-    const int unit = (int)blockIdx.x * G + grp;
+    const int unit = block * G + grp;
     const int p = LPP == 64 ? unit / nseg : unit;
     const int s = LPP == 64 ? unit - p * nseg : 0;
     const bool live = p < P;
@@ -551,6 +768,28 @@ __global__ __launch_bounds__(64) void k_foot(FootArgs a) {
         lane_sync();
     }
     if (live && sub == 0) a.P.list_len[(int64_t)p * nseg + s] = total;
+}
+
+// Footprints and, in the workgroups before them, the contacts of the step
+// (ndem workgroups; THREAD: one thread per particle, else one wavefront): both
+// read the particles only, and one launch keeps the step on one stream (a fork
+// to a second stream and back cost about 10 us each way in the step's chain).
+// Five wavefronts per SIMD (92 registers for spheres; 118 without the bound).
+// 8 317 spheres: 62 us for both, where the footprint alone took 58 beside the
+// cell list and the contacts (63 us) on a second stream; 21 361 discs 38 us.
+template <int D, int S, int LPP, bool THREAD>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPP == 64 ? 5 : 4))) void k_foot(FootArgs a, CellArgs c, int ndem) {
+    constexpr size_t FB = sizeof(FootLds<D, LPP>);
+    constexpr size_t DB = THREAD ? sizeof(int[MAX_CONTACTS][64]) : sizeof(int[MAX_CONTACTS + 1]);
+    __shared__ __attribute__((aligned(16))) char lds[FB > DB ? FB : DB];
+    const int b = (int)blockIdx.x;
+    if (b < ndem) {
+        int *list = (int *)lds;
+        if (THREAD) dem_thread<64>(c, b * 64 + (int)threadIdx.x, (int(*)[64])list);
+        else dem_wave(c, b, list, list + MAX_CONTACTS);
+        return;
+    }
+    foot_segment<D, S, LPP>(a, b - ndem, *(FootLds<D, LPP> *)lds);
 }
 
 // Footprints of every particle (one workgroup each), or of the particles of
@@ -779,48 +1018,59 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
 #pragma unroll
         for (int c = 0; c < NC; c++) val[c] = __shfl(t.s + t.c, c, 64);
     }
-    double pv[3], pw[3], pfc[3];
-    for (int d = 0; d < 3; d++) {
-        pv[d] = __shfl(pre, gbase + d, 64);
-        pw[d] = __shfl(pre, gbase + 3 + d, 64);
-        pfc[d] = __shfl(pre, gbase + 6 + d, 64);
-    }
+    // axis d is lane d's from here on
+    const int d = sub % LPP < 3 ? sub % LPP : 2;
+    const double pv = __shfl(pre, gbase + d, 64), pw = __shfl(pre, gbase + 3 + d, 64);
+    const double pfc = __shfl(pre, gbase + 6 + d, 64);
     const double pm = __shfl(pre, gbase + 9, 64), pI = __shfl(pre, gbase + 10, 64);
     const double pfix = __shfl(pre, gbase + 11, 64);
-    if (live && sub == 0) {
-        double Fv[3], Tv[3];
-        for (int d = 0; d < 3; d++) {
-            Fv[d] = D == 3 ? -val[d] : (d < 2 ? -val[d] : 0.0);
-            Tv[d] = D == 3 ? -val[(3 + d) % NC] : (d == 2 ? -val[2] : 0.0);
-            a.P.Fh[d * P + p] = Fv[d];
-            a.P.Th[d * P + p] = Tv[d];
-        }
+    const double xo = d == 0 ? xp0 : (d == 1 ? xp1 : xp2);
+    double Fv = 0.0, Tv = 0.0;
+    if (D == 3) {
+        Fv = -(d == 0 ? val[0] : (d == 1 ? val[1] : val[2]));
+        Tv = -(d == 0 ? val[3 % NC] : (d == 1 ? val[4 % NC] : val[5 % NC]));
+    } else {
+        if (d < 2) Fv = -(d == 0 ? val[0] : val[1]);
+        if (d == 2) Tv = -val[2];
+    }
+    const bool mine = live && sub < 3;
+    double vn = pv, xn = xo;
+    if (mine) {
+        a.P.Fh[d * P + p] = Fv;
+        a.P.Th[d * P + p] = Tv;
         // Symplectic Euler with dt = 1 for this particle (every reader of its
         // position in this kernel has read it): v += (F^h + F^c + m a)/m,
         // omega += T^h/I, x += v (new), periodic wrap.
         if (a.integrate && pfix == 0.0) {
-            const double xo[3] = {xp0, xp1, xp2};
-            for (int d = 0; d < D; d++) {
-                const double ftot = Fv[d] + pfc[d] + pm * a.ap[d];
-                const double vn = pv[d] + ftot / pm;
+            if (d < D) {
+                const double ftot = Fv + pfc + pm * a.ap[d];
+                vn = pv + ftot / pm;
                 a.P.v[d * P + p] = vn;
-                double xn = xo[d] + vn;
+                xn = xo + vn;
                 if (!(d == 1 && a.g.wall_y)) xn = wrap_pos(xn, d == 0 ? a.g.Lx : (d == 1 ? a.g.Ly : a.g.Lz));
                 a.P.x[d * P + p] = xn;
             }
-            if (D == 3) {
-                for (int d = 0; d < 3; d++) a.P.w[d * P + p] = pw[d] + Tv[d] / pI;
-            } else {
-                a.P.w[2 * P + p] = pw[2] + Tv[2] / pI;
-            }
+            if (D == 3 || d == 2) a.P.w[d * P + p] = pw + Tv / pI;
             // the slab pipeline assumes at most one node of motion in y per step
-            if (a.G.K > 1 && !(fabs(a.P.v[P + p]) <= 1.0)) atomicOr(a.flags, FLAG_FAST);
+            if (d == 1 && a.G.K > 1 && !(fabs(vn) <= 1.0)) atomicOr(a.flags, FLAG_FAST);
         }
-        if (a.integrate && a.G.K > 1) {
-            // file the particle in its group of the next step
-            const int gn = slab_group(a.G, a.P.x[P + p], a.P.R[p]);
-            const int slot = atomicAdd(&a.G.ncount[gn], 1);
-            a.G.nlist[(int64_t)gn * a.G.stride + slot] = p;
+    }
+    if (a.integrate && a.G.K > 1 && mine && d == 1) {
+        // file the particle in its group of the next step
+        const int gn = slab_group(a.G, xn, a.P.R[p]);
+        const int slot = atomicAdd(&a.G.ncount[gn], 1);
+        a.G.nlist[(int64_t)gn * a.G.stride + slot] = p;
+    }
+    if (a.file) {
+        // file the particle in the cell list of the next step, and clear the
+        // count of the cell that held it in this one (its contacts are done)
+        const int nc = d == 0 ? a.nc[0] : (d == 1 ? a.nc[1] : a.nc[2]);
+        const int was = d < D ? cell_coord(a.g, nc, d, xo) : 0, is = d < D ? cell_coord(a.g, nc, d, xn) : 0;
+        const int w1 = __shfl(was, gbase + 1, 64), w2 = __shfl(was, gbase + 2, 64);
+        const int i1 = __shfl(is, gbase + 1, 64), i2 = __shfl(is, gbase + 2, 64);
+        if (live && sub == 0) {
+            a.cell_old[was + a.nc[0] * (w1 + a.nc[1] * w2)] = 0;
+            file_in_cell(a.cell_new, a.cell_ids, a.flags, is + a.nc[0] * (i1 + a.nc[1] * i2), p);
         }
     }
 }
@@ -880,203 +1130,6 @@ __global__ void k_list_q(ForceArgs a, double *out) {
             for (int d = 0; d < D; d++) out[d * N + n] = qq[d];
         }
     }
-}
-
-// ------------------------------------------------------------- cell list
-__device__ __forceinline__ int cell_coord(const CellArgs &a, int axis, double x) {
-    const int nc = axis == 0 ? a.ncx : (axis == 1 ? a.ncy : a.ncz);
-    const double L = axis == 0 ? a.g.Lx : (axis == 1 ? a.g.Ly : a.g.Lz);
-    double t = x;
-    if (axis == 1 && a.g.wall_y) t = x + 0.5;
-    int c = (int)floor(t * (double)nc / L);
-    return c < 0 ? 0 : (c >= nc ? nc - 1 : c);
-}
-
-__global__ void k_cells(CellArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    const int P = a.P.np;
-    if (p >= P) return;
-    const int cx = cell_coord(a, 0, a.P.x[p]);
-    const int cy = cell_coord(a, 1, a.P.x[P + p]);
-    const int cz = a.D == 3 ? cell_coord(a, 2, a.P.x[2 * P + p]) : 0;
-    const int c = cx + a.ncx * (cy + a.ncy * cz);
-    const int slot = atomicAdd(&a.cell_count[c], 1);
-    if (slot < CELL_CAP) a.cell_ids[c * CELL_CAP + slot] = p;
-    else atomicOr(a.flags, FLAG_CELL_OVERFLOW);
-}
-
-// Neighbour cell offsets along one axis: {-1,0,1} wrapped (periodic, >= 3
-// cells), {0,1} (2 cells), {0} (1 cell), or {-1,0,1} clipped at walls.
-__device__ __forceinline__ int axis_cells(int c, int nc, bool periodic, int out[3]) {
-    if (periodic) {
-        if (nc >= 3) { out[0] = c == 0 ? nc - 1 : c - 1; out[1] = c; out[2] = c == nc - 1 ? 0 : c + 1; return 3; }
-        if (nc == 2) { out[0] = 0; out[1] = 1; return 2; }
-        out[0] = 0;
-        return 1;
-    }
-    int k = 0;
-    for (int d = -1; d <= 1; d++)
-        if (c + d >= 0 && c + d < nc) out[k++] = c + d;
-    return k;
-}
-
-// Contact test and force of Eqs. 4-5 for the pair (i, j) with the overlap
-// delta = R_i + R_j - |r_i - r_j| (minimum image).  Returns false when the
-// particles do not touch.
-__device__ __forceinline__ bool pair_force(const CellArgs &a, int i, int j, double F[3]) {
-    const int P = a.P.np, D = a.D;
-    double d[3] = {0.0, 0.0, 0.0};
-    for (int ax = 0; ax < D; ax++) {
-        double dd = a.P.x[ax * P + i] - a.P.x[ax * P + j];
-        if (!(ax == 1 && a.g.wall_y)) dd = pdisp(dd, ax == 0 ? a.g.Lx : (ax == 1 ? a.g.Ly : a.g.Lz));
-        d[ax] = dd;
-    }
-    double d2 = d[0] * d[0] + d[1] * d[1];
-    if (D == 3) d2 = d2 + d[2] * d[2];
-    const double dist = sqrt(d2);
-    const double delta = (a.P.R[i] + a.P.R[j]) - dist;
-    if (!(delta > 0.0)) return false;
-    if (F) {
-        double nrm[3] = {0.0, 0.0, 0.0};
-        for (int ax = 0; ax < D; ax++) nrm[ax] = d[ax] / dist;
-        double vn = (a.P.v[i] - a.P.v[j]) * nrm[0] + (a.P.v[P + i] - a.P.v[P + j]) * nrm[1];
-        if (D == 3) vn = vn + (a.P.v[2 * P + i] - a.P.v[2 * P + j]) * nrm[2];
-        const double meff = a.P.m[i] * a.P.m[j] / (a.P.m[i] + a.P.m[j]);
-        const double eta = a.ce * sqrt(meff * a.kn);
-        const double fmag = a.kn * delta - eta * vn;
-        for (int ax = 0; ax < D; ax++) F[ax] = F[ax] + fmag * nrm[ax];
-    }
-    return true;
-}
-
-// Wall contacts of particle i (Eqs. 4-5 against a wall at rest, m_eff = m_i),
-// added to F after the pair forces.
-__device__ __forceinline__ void wall_force(const CellArgs &a, int i, double F[3]) {
-    if (!a.g.wall_y) return;
-    const int P = a.P.np;
-    const double eta = a.ce * sqrt(a.P.m[i] * a.kn);
-    const double y = a.P.x[P + i];
-    const double vy = a.P.v[P + i];
-    const double dl = a.P.R[i] - (y + 0.5);
-    if (dl > 0.0) {
-        const double fmag = a.kn * dl - eta * vy;
-        F[1] = F[1] + fmag;
-    }
-    const double du = a.P.R[i] - ((a.g.Ly - 0.5) - y);
-    if (du > 0.0) {
-        const double fmag = a.kn * du - eta * (-vy);
-        F[1] = F[1] - fmag;
-    }
-}
-
-// One wavefront per particle: each lane scans one neighbour cell, touching
-// neighbours are gathered in LDS, sorted by id, and the pair forces are added
-// in ascending id (then the walls) by the first lane.
-__global__ __launch_bounds__(256) void k_dem(CellArgs a) {
-    __shared__ int list[4][MAX_CONTACTS];
-    __shared__ int nlist[4];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int i = blockIdx.x * 4 + wave;
-    const int P = a.P.np;
-    const int D = a.D;
-    if (lane == 0) nlist[wave] = 0;
-    __syncthreads();
-    if (i < P) {
-        const int c0 = cell_coord(a, 0, a.P.x[i]);
-        const int c1 = cell_coord(a, 1, a.P.x[P + i]);
-        const int c2 = D == 3 ? cell_coord(a, 2, a.P.x[2 * P + i]) : 0;
-        int ox[3], oy[3], oz[3];
-        const int nxc = axis_cells(c0, a.ncx, true, ox);
-        const int nyc = axis_cells(c1, a.ncy, !a.g.wall_y, oy);
-        int nzc = 1;
-        oz[0] = 0;
-        if (D == 3) nzc = axis_cells(c2, a.ncz, true, oz);
-        if (lane < nxc * nyc * nzc) {
-            const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
-            const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-            const int cnt = min(a.cell_count[c], CELL_CAP);
-            for (int s = 0; s < cnt; s++) {
-                const int j = a.cell_ids[c * CELL_CAP + s];
-                if (j == i) continue;
-                if (!pair_force(a, i, j, nullptr)) continue;
-                const int slot = atomicAdd(&nlist[wave], 1);
-                if (slot < MAX_CONTACTS) list[wave][slot] = j;
-                else atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
-            }
-        }
-    }
-    __syncthreads();
-    if (i < P && lane == 0) {
-        int *l = list[wave];
-        const int nl = min(nlist[wave], MAX_CONTACTS);
-        for (int s = 1; s < nl; s++) {
-            const int v = l[s];
-            int t = s - 1;
-            while (t >= 0 && l[t] > v) {
-                l[t + 1] = l[t];
-                t--;
-            }
-            l[t + 1] = v;
-        }
-        double F[3] = {0.0, 0.0, 0.0};
-        for (int s = 0; s < nl; s++) pair_force(a, i, l[s], F);
-        wall_force(a, i, F);
-        for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
-    }
-}
-
-// One thread per particle, for many particles (k_dem keeps a wavefront busy
-// with 9 or 27 neighbour cells, most of its lanes idle in 2D): the thread
-// walks the neighbour cells itself and inserts each touching neighbour into
-// its own id-sorted column of LDS, then adds the pair forces in ascending id
-// and the walls, the sum order of k_dem, so both kernels give the same bits.
-template <int NT>
-__global__ __launch_bounds__(NT) void k_dem_thread(CellArgs a) {
-    __shared__ int list[MAX_CONTACTS][NT];
-    const int t = threadIdx.x;
-    const int i = blockIdx.x * NT + t;
-    const int P = a.P.np;
-    const int D = a.D;
-    if (i >= P) return;  // no barrier below
-    const int c0 = cell_coord(a, 0, a.P.x[i]);
-    const int c1 = cell_coord(a, 1, a.P.x[P + i]);
-    const int c2 = D == 3 ? cell_coord(a, 2, a.P.x[2 * P + i]) : 0;
-    int ox[3], oy[3], oz[3];
-    const int nxc = axis_cells(c0, a.ncx, true, ox);
-    const int nyc = axis_cells(c1, a.ncy, !a.g.wall_y, oy);
-    int nzc = 1;
-    oz[0] = 0;
-    if (D == 3) nzc = axis_cells(c2, a.ncz, true, oz);
-    int nl = 0;
-    bool overflow = false;
-    for (int kz = 0; kz < nzc; kz++)
-        for (int ky = 0; ky < nyc; ky++)
-            for (int kx = 0; kx < nxc; kx++) {
-                const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-                const int cnt = min(a.cell_count[c], CELL_CAP);
-                for (int s = 0; s < cnt; s++) {
-                    const int j = a.cell_ids[c * CELL_CAP + s];
-                    if (j == i) continue;
-                    if (!pair_force(a, i, j, nullptr)) continue;
-                    if (nl >= MAX_CONTACTS) {
-                        overflow = true;
-                        continue;
-                    }
-                    int q = nl;
-                    while (q > 0 && list[q - 1][t] > j) {
-                        list[q][t] = list[q - 1][t];
-                        q--;
-                    }
-                    list[q][t] = j;
-                    nl++;
-                }
-            }
-    if (overflow) atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
-    double F[3] = {0.0, 0.0, 0.0};
-    for (int s = 0; s < nl; s++) pair_force(a, i, list[s][t], F);
-    wall_force(a, i, F);
-    for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
 }
 
 // ------------------------------------------------------ neighbour-list mode
@@ -1231,10 +1284,13 @@ static unsigned blocks_for(int n, int per) { return (unsigned)((n + per - 1) / p
 // workgroups of a launch that walks one group's list
 constexpr int GROUP_GRID = 4096;
 
-// 2D runs of this many discs keep 16 lanes per disc, four discs per wavefront
-// (1 166 400 discs: 1.96 against 2.75 ms with a wavefront each); with fewer, a
-// wavefront or several per disc shorten the chain (16 discs: 5.4 against 22.6 us).
-constexpr int FOOT_SUB_MIN = 16384;
+// 2D runs of this many discs keep 16 lanes per disc in the footprint, four discs
+// per wavefront (1 166 400 discs: 1.96 against 2.75 ms with a wavefront each),
+// and a thread per disc for the contacts (21 361 discs 25 against 65 us,
+// 1 166 400 discs 0.54 against 4.4 ms).  With fewer, a wavefront or several per
+// disc shorten the chain (16 discs: footprint 5.4 against 22.6 us); 8 317
+// spheres with a thread each took 168 against 26 us.
+constexpr int DISC_MANY = 16384;
 
 template <int D, int NT, bool TAB>
 static hipError_t paint_s(const FootArgs &a, hipStream_t s) {
@@ -1263,18 +1319,19 @@ static hipError_t paint_s(const FootArgs &a, hipStream_t s) {
 #define FOOT_NT3 128
 #endif
 
-template <int D, int LPP>
-static hipError_t paint_plain(const FootArgs &a, hipStream_t s) {
-    const dim3 g((unsigned)(LPP == 64 ? (int64_t)a.P.np * a.P.nseg : blocks_for(a.P.np, 64 / LPP))), b(64);
+template <int D, int LPP, bool THREAD>
+static hipError_t paint_plain(const FootArgs &a, const CellArgs &c, bool dem, hipStream_t s) {
+    const int ndem = !dem ? 0 : (THREAD ? (int)blocks_for(a.P.np, 64) : a.P.np);
+    const dim3 g((unsigned)(ndem + (LPP == 64 ? (int64_t)a.P.np * a.P.nseg : blocks_for(a.P.np, 64 / LPP)))), b(64);
     switch (a.S) {
-        case 1: hipLaunchKernelGGL((k_foot<D, 1, LPP>), g, b, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_foot<D, 2, LPP>), g, b, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_foot<D, 3, LPP>), g, b, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_foot<D, 4, LPP>), g, b, 0, s, a); break;
-        case 5: hipLaunchKernelGGL((k_foot<D, 5, LPP>), g, b, 0, s, a); break;
-        case 6: hipLaunchKernelGGL((k_foot<D, 6, LPP>), g, b, 0, s, a); break;
-        case 7: hipLaunchKernelGGL((k_foot<D, 7, LPP>), g, b, 0, s, a); break;
-        default: hipLaunchKernelGGL((k_foot<D, 8, LPP>), g, b, 0, s, a); break;
+        case 1: hipLaunchKernelGGL((k_foot<D, 1, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 2: hipLaunchKernelGGL((k_foot<D, 2, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 3: hipLaunchKernelGGL((k_foot<D, 3, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 4: hipLaunchKernelGGL((k_foot<D, 4, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 5: hipLaunchKernelGGL((k_foot<D, 5, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 6: hipLaunchKernelGGL((k_foot<D, 6, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        case 7: hipLaunchKernelGGL((k_foot<D, 7, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
+        default: hipLaunchKernelGGL((k_foot<D, 8, LPP, THREAD>), g, b, 0, s, a, c, ndem); break;
     }
     return hipGetLastError();
 }
@@ -1289,16 +1346,22 @@ int foot_segments(int D, int np, double rmax) {
     return nseg;
 }
 
+static hipError_t paint_any(const FootArgs &a, const CellArgs &c, bool dem, int D, hipStream_t s) {
+    if (D == 3) return paint_plain<3, 64, false>(a, c, dem, s);
+    return a.P.np >= DISC_MANY ? paint_plain<2, 16, true>(a, c, dem, s) : paint_plain<2, 64, false>(a, c, dem, s);
+}
+
 hipError_t launch_foot_paint(const FootArgs &a, int D, hipStream_t s) {
     if (a.P.np == 0) return hipSuccess;
     // the table lookup is a kernel of its own, so the sampling kernel keeps
     // its registers
     if (a.tab) return D == 2 ? paint_s<2, FOOT_NT2, true>(a, s) : paint_s<3, FOOT_NT3, true>(a, s);
-    if (a.G.g < 0) {
-        if (D == 3) return paint_plain<3, 64>(a, s);
-        return a.P.np >= FOOT_SUB_MIN ? paint_plain<2, 16>(a, s) : paint_plain<2, 64>(a, s);
-    }
+    if (a.G.g < 0) return paint_any(a, CellArgs{}, false, D, s);
     return D == 2 ? paint_s<2, FOOT_NT2, false>(a, s) : paint_s<3, FOOT_NT3, false>(a, s);
+}
+
+hipError_t launch_foot_dem(const FootArgs &a, const CellArgs &c, int D, hipStream_t s) {
+    return a.P.np == 0 ? hipSuccess : paint_any(a, c, true, D, s);
 }
 
 template <int D, int NT>
@@ -1373,17 +1436,9 @@ hipError_t launch_cells(const CellArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Contacts: a thread per particle for 2D runs of at least DEM_THREAD_MIN
-// discs, else a wavefront per particle.  Measured on MI355X: 21 361 discs
-// 25 against 65 us, 1 166 400 discs 0.54 against 4.4 ms; 8 317 spheres 168
-// against 26 us (too few wavefronts to hide a thread's walk over 27 cells).
-#ifndef DEM_THREAD_MIN
-#define DEM_THREAD_MIN 16384
-#endif
-
 hipError_t launch_dem(const CellArgs &a, hipStream_t s) {
     if (a.P.np == 0) return hipSuccess;
-    if (a.D == 2 && a.P.np >= DEM_THREAD_MIN)
+    if (a.D == 2 && a.P.np >= DISC_MANY)
         hipLaunchKernelGGL(k_dem_thread<128>, dim3(blocks_for(a.P.np, 128)), dim3(128), 0, s, a);
     else
         hipLaunchKernelGGL(k_dem, dim3(blocks_for(a.P.np, 4)), dim3(256), 0, s, a);

@@ -83,3 +83,43 @@ def test_particle_count_does_not_change_a_particle(gpu_lib):
         sim.close()
     # the last disc changes its own surroundings only; the others' first step is local
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+def test_cell_list_carried_between_steps(gpu_lib, dim):
+    """The plain step files each particle in the next step's cell list; steps
+    with every phase timed, with neighbour lists or with the slab pipeline
+    build their own.  Contacts across all switches, and after the particle set
+    and a saved state are replaced, equal the oracle bit for bit."""
+    shape = (60, 80) if dim == 2 else (30, 44, 28)
+    R = 3.0
+    n = 40 if dim == 2 else 60
+    radii = [R] * n
+    parts = particles(dim, shape, radii, 500 + dim, True)
+    parts[1][:] *= 20.0  # fast enough to change cells and touch within some steps
+    orc, gpu = make_pair(gpu_lib, dim, shape, 0.7, wall_y=True, particle_accel=(0, -1e-4, 0), samples=4, kn=40.0,
+                         restitution=0.9, particles=parts, max_radius=R)
+    touched = 0
+    switches = [lambda: None, lambda: gpu.set_timing(True), lambda: gpu.set_timing(False),
+                lambda: gpu.set_neighbour_list(5, 1.0), lambda: gpu.set_neighbour_list(0),
+                lambda: gpu.set_pipeline(2), lambda: gpu.set_pipeline(1), lambda: gpu.set_timing(True, lattice_only=True)]
+    for k, switch in enumerate(switches):
+        print("cell list, %dD, switch %d" % (dim, k), flush=True)
+        switch()
+        for chunk in (1, 4, 3):
+            orc.step(chunk)
+            gpu.step(chunk)
+            errs = compare(orc, gpu)
+            assert all(e == 0.0 for e in errs.values()), (k, errs)
+            touched += int(np.count_nonzero(np.abs(orc.contact_forces()).sum(axis=1)))
+    assert touched > 0
+    import os
+    import tempfile
+    path = os.path.join(tempfile.mkdtemp(), "state")
+    gpu.save(path)
+    gpu.step(6)
+    orc.step(3)
+    gpu.load_state(path)
+    gpu.step(3)
+    errs = compare(orc, gpu)
+    assert all(e == 0.0 for e in errs.values()), errs
