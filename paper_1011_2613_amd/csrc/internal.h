@@ -73,6 +73,7 @@ struct Particles {
 constexpr int FOOT_SEG_MAX = 256;
 constexpr int FOOT_SEG_UNITS = 4096;
 int foot_segments(int D, int np, double rmax);
+constexpr int FORCE_PARTS = 1024;  // workgroups of all particles that share particles, at most
 
 // Entries between the starts of two segments of particle p's list: its
 // bounding box's items split evenly.
@@ -192,6 +193,9 @@ struct ForceArgs {
     int integrate;         // 1: the kernel also advances the particle (needs F^c of this step)
     double ap[3];          // particle acceleration (gravity with buoyancy)
     int entries;           // list entries of the largest particle, about
+    int parts;             // workgroups per particle (set by launch_force)
+    double *part;          // [np][parts] sums of the workgroups of a particle (12 values at most)
+    int *arrived;          // [np] workgroups that have left theirs; zero between steps
     int file;              // 1: file the particle in the next step's cell list too
     int nc[3];             // cells per axis
     int *cell_old, *cell_new, *cell_ids;  // counts of this and the next step's list

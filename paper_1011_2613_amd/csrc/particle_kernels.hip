@@ -881,17 +881,19 @@ constexpr int acc_place(int c) {
 }
 
 // NT threads per particle over its footprint list (NT <= 64: an aligned run of
-// lanes of a wavefront; above: a workgroup): each entry gives the node and the
+// lanes of a wavefront; above: a workgroup, or with `parts` > 1 workgroups that
+// take a share of the list each, this one's index being `part`): each entry gives the node and the
 // particle's sample count there; q_n and the node's total count come from the
 // lattice kernel.  s_pn q_n and r_pn x (s_pn q_n) go into TwoSum accumulators,
-// which are merged over the lanes, then over the wavefronts in turn.
-// F_p = -sum, T_p = -sum.  With `integrate` set, the first thread then advances
+// which are merged over the lanes, then over the wavefronts in turn, then over
+// the workgroups in turn by the one that finishes last (each leaves its sums
+// and counts itself in; nothing waits).  F_p = -sum, T_p = -sum.  With `integrate` set, the first thread then advances
 // the particle (the contact forces of the step are complete).  `sub` is the
 // thread's index among the particle's; `live` is false for the runs past the
 // last particle, which take part in the shuffles only.
 template <int D, bool R32, int NT>
-__device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, bool live) {
-    static_assert(NT >= 16 && NT <= 1024 && (NT & (NT - 1)) == 0, "threads per particle");
+__device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, bool live, int part = 0) {
+    static_assert(NT >= 16 && NT <= 256 && (NT & (NT - 1)) == 0, "threads per particle");
     constexpr int LPP = NT < 64 ? NT : 64, W = NT / LPP;  // lanes per wavefront, wavefronts
     constexpr int NC = D == 3 ? 6 : 3;                    // F_x, F_y, F_z, T_x, T_y, T_z or F_x, F_y, T_z
     const int lane = threadIdx.x & 63;
@@ -925,8 +927,9 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
     // one segment: every thread of the particle, or with several segments one
     // wavefront each in turn
     const int seg = nseg > 1 ? list_seg(a.P, q) : 0;
-    const int first = nseg > 1 ? sub % LPP : sub, width = nseg > 1 ? LPP : NT;
-    for (int s = nseg > 1 ? sub / LPP : 0; s < nseg; s += W) {
+    const int parts = NT > 64 ? a.parts : 1;
+    const int first = nseg > 1 ? sub % LPP : part * NT + sub, width = nseg > 1 ? LPP : parts * NT;
+    for (int s = nseg > 1 ? part * W + sub / LPP : 0; s < nseg; s += parts * W) {
         const uint32_t *list = a.P.list + (int64_t)q * cap + s * seg;
         const int room = cap - s * seg;  // entries of the particle's list from here on
         const int len = live ? a.P.list_len[(int64_t)q * nseg + s] : 0;
@@ -1007,14 +1010,39 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
 #pragma unroll
         for (int c = 0; c < NC; c++) val[c] = __shfl(mine, gbase + acc_place<LPP, NC>(c), 64);
     } else {
-        __shared__ Acc part[W][NC];
+        __shared__ Acc wsum[W][NC];
 #pragma unroll
         for (int c = 0; c < NC; c++)
-            if (lane == acc_place<LPP, NC>(c)) part[sub / LPP][c] = A[0];
+            if (lane == acc_place<LPP, NC>(c)) wsum[sub / LPP][c] = A[0];
         __syncthreads();
         if (sub >= 64) return;
-        Acc t = part[0][lane < NC ? lane : 0];
-        for (int w = 1; w < W; w++) acc_merge(t, part[w][lane < NC ? lane : 0]);
+        const int c0 = lane < NC ? lane : 0;
+        Acc t = wsum[0][c0];
+        for (int w = 1; w < W; w++) acc_merge(t, wsum[w][c0]);
+        if (parts > 1) {
+            // the other workgroups may run on another XCD: agent scope throughout
+            double *const sums = a.part + (int64_t)p * parts * 2 * NC + 2 * c0;
+            if (lane < NC) {
+                __hip_atomic_store(sums + part * 2 * NC, t.s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(sums + part * 2 * NC + 1, t.c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            int before = 0;
+            if (lane == 0)
+                before = __hip_atomic_fetch_add(&a.arrived[p], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            if (__shfl(before, 0, 64) != parts - 1) return;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (lane == 0) a.arrived[p] = 0;  // for the next step
+            // lane 8 g + c adds component c of the workgroups g, g + 8, ..., then
+            // the eight lanes of a component merge
+            const double *const from = a.part + (int64_t)p * parts * 2 * NC + 2 * ((lane & 7) < NC ? lane & 7 : 0);
+            t = Acc{0.0, 0.0};
+            for (int b = lane >> 3; b < parts; b += 8)
+                acc_merge(t, Acc{__hip_atomic_load(from + b * 2 * NC, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                                 __hip_atomic_load(from + b * 2 * NC + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)});
+#pragma unroll
+            for (int m = 8; m < 64; m <<= 1) acc_merge(t, Acc{shfl_xor_d(t.s, m), shfl_xor_d(t.c, m)});
+        }
 #pragma unroll
         for (int c = 0; c < NC; c++) val[c] = __shfl(t.s + t.c, c, 64);
     }
@@ -1076,14 +1104,18 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
 }
 
 // Force, torque and integration of every particle: 64 / NT particles per
-// wavefront and one wavefront per workgroup, or one workgroup of NT threads per
-// particle.
+// wavefront and one wavefront per workgroup, or a.parts workgroups of NT
+// threads per particle.
 template <int D, bool R32, int NT>
 __global__ __launch_bounds__(NT < 64 ? 64 : NT) void k_force(ForceArgs a) {
-    constexpr int G = NT < 64 ? 64 / NT : 1;
     const int t = (int)threadIdx.x;
-    const int p = (int)blockIdx.x * G + t / NT;
-    force_unit<D, R32, NT>(a, p, t % NT, p < a.P.np);
+    if (NT > 64) {
+        const int p = (int)blockIdx.x / a.parts;
+        force_unit<D, R32, NT>(a, p, t, true, (int)blockIdx.x - p * a.parts);
+    } else {
+        const int p = (int)blockIdx.x * (64 / NT) + t / NT;
+        force_unit<D, R32, NT>(a, p, t % NT, p < a.P.np);
+    }
 }
 
 // The same for the particles of group G.g, one wavefront each; workgroups walk
@@ -1374,22 +1406,24 @@ static void force_nt(const ForceArgs &a, dim3 g, hipStream_t s) {
 // Threads per particle of the force kernel on the plain step: 16 per disc and
 // 64 per sphere on many particles (1 166 400 discs: 1.18 against 1.62 ms with 64
 // lanes each; spheres within 3 % with 16 or 32), four times as many while that
-// leaves fewer than four wavefronts per SIMD and a thread still has an entry:
-// with few particles the walk over the list bounds the step (one sphere R = 16
-// 46 us with 1 024 threads against 240 with 64, 310 spheres R = 5.3 11 us with
-// 256 against 18 with 64, 16 discs R = 6 8.1 us with 64 against 10.7 with 16).
+// leaves fewer than four wavefronts per SIMD and a thread still has an entry;
+// beyond 256, several workgroups per particle, an entry per thread.  With few
+// particles the walk over the list bounds the step: one sphere R = 16 10.4 us
+// with 64 workgroups against 46 with 1 024 threads and 240 with 64, 310 spheres R = 5.3 11 us
+// with 256 against 18 with 64, 16 discs R = 6 8.1 us with 64 against 10.7 with 16.
 // The slab pipeline's groups take one wavefront per particle.
 static int force_threads(const ForceArgs &a) {
     int nt = a.D == 2 ? 16 : 64;
-    while (nt < 1024 && (int64_t)a.P.np * nt < 262144 && 4 * nt <= a.entries) nt *= 4;
+    while (nt < 256 && (int64_t)a.P.np * nt < 262144 && 4 * nt <= a.entries) nt *= 4;
     return nt;
 }
 
-hipError_t launch_force(const ForceArgs &a, hipStream_t s) {
+hipError_t launch_force(const ForceArgs &args, hipStream_t s) {
+    ForceArgs a = args;
+    a.parts = 1;
     if (a.P.np == 0) return hipSuccess;
     if (a.G.g >= 0) {
-        const dim3 g((unsigned)std::min(a.P.np, GROUP_GRID));
-        const dim3 b(64);
+        const dim3 g((unsigned)std::min(a.P.np, GROUP_GRID)), b(64);
         if (a.D == 2) {
             if (a.rec32) hipLaunchKernelGGL((k_force_group<2, true>), g, b, 0, s, a);
             else hipLaunchKernelGGL((k_force_group<2, false>), g, b, 0, s, a);
@@ -1400,16 +1434,15 @@ hipError_t launch_force(const ForceArgs &a, hipStream_t s) {
         return hipGetLastError();
     }
     const int nt = force_threads(a);
-    const dim3 g(blocks_for(a.P.np, nt < 64 ? 64 / nt : 1));
+    if (nt == 256) a.parts = std::max(1, std::min({a.entries / 256, FORCE_PARTS / a.P.np, 64}));
+    const dim3 g(nt > 64 ? (unsigned)(a.P.np * a.parts) : blocks_for(a.P.np, 64 / nt));
     if (a.D == 2) {
         if (nt == 16) force_nt<2, 16>(a, g, s);
         else if (nt == 64) force_nt<2, 64>(a, g, s);
-        else if (nt == 256) force_nt<2, 256>(a, g, s);
-        else force_nt<2, 1024>(a, g, s);
+        else force_nt<2, 256>(a, g, s);
     } else {
         if (nt == 64) force_nt<3, 64>(a, g, s);
-        else if (nt == 256) force_nt<3, 256>(a, g, s);
-        else force_nt<3, 1024>(a, g, s);
+        else force_nt<3, 256>(a, g, s);
     }
     return hipGetLastError();
 }

@@ -40,7 +40,7 @@ struct Layout {
     int list_cap;
     double rmax;
     size_t off_cc, off_cc2, off_cid, off_flags, off_tab, off_stats, off_nl, off_nl_len, off_xb, off_nl_state;
-    size_t off_gcount, off_glist, list_buf, total;
+    size_t off_gcount, off_glist, off_fpart, off_arrived, list_buf, total;
 };
 
 int validate(const lbm_config *c, std::string &msg) {
@@ -126,6 +126,9 @@ Layout make_layout(const lbm_config *c) {
     // slab pipeline: group counts and lists of two steps
     L.off_gcount = take(2 * PIPE_MAX * 4);
     L.off_glist = take(2 * (size_t)PIPE_MAX * P * 4);
+    // force sums shared by several workgroups: their partial sums and arrivals
+    L.off_fpart = take((size_t)FORCE_PARTS * 12 * 8);
+    L.off_arrived = take((size_t)FORCE_PARTS * 4);
     L.total = o;
     return L;
 }
@@ -142,10 +145,11 @@ struct lbm_ctx {
     Layout L;
     char *ws;
     hipStream_t stream;
-    hipStream_t cap_stream;
-    // the DEM cell list and contact forces run on a side stream beside the
-    // footprint, lattice and force kernels (they only read positions and
-    // velocities, which change in the integration at the end of the step)
+    hipStream_t cap_stream;   // graphs are captured on it; null until the first
+    // where they are not part of the footprint launch, the DEM cell list and
+    // contact forces run on a side stream beside the footprint, lattice and
+    // force kernels (they only read positions and velocities, which change in
+    // the integration at the end of the step); null until a step needs it
     hipStream_t side_stream;
     static constexpr int GS = 8;  // event slots (steps in flight at once in the pipeline)
     hipEvent_t ev_fork[GS], ev_join[GS], ev_L[GS][PIPE_MAX], ev_P[GS][PIPE_MAX];
@@ -476,6 +480,8 @@ ForceArgs force_args(lbm_ctx *c, int buf, const Groups &G) {
     fo.entries = (int)(c->L.D == 2 ? M_PI * c->prmax * c->prmax : 4.0 / 3.0 * M_PI * std::pow(c->prmax, 3));
     fo.flags = flags(c);
     fo.G = G;
+    fo.part = wsp<double>(c, c->L.off_fpart);
+    fo.arrived = wsp<int>(c, c->L.off_arrived);
     fo.file = 0;
     fo.nc[0] = c->ncx; fo.nc[1] = c->ncy; fo.nc[2] = c->ncz;
     fo.cell_old = wsp<int>(c, buf == 0 ? c->L.off_cc : c->L.off_cc2);
@@ -648,13 +654,14 @@ hipError_t enqueue_step(lbm_ctx *c, int from, hipStream_t s, int slot, bool firs
     return enqueue_plain(c, from, s, slot);
 }
 
-// The step events (fork/join, lattice slabs, particle groups) of every
-// slot; events that were not created are null.
-bool create_step_events(lbm_ctx *c) {
-    bool ok = true;
+// The second stream and the step events (fork/join, lattice slabs, particle
+// groups) of every slot, created by the first step that uses them (outside any
+// capture): most contexts run on one stream.
+hipError_t need_side_stream(lbm_ctx *c) {
+    if (c->side_stream) return hipSuccess;
+    hipError_t e = hipSuccess;
     auto mk = [&](hipEvent_t &ev) {
-        ev = nullptr;
-        if (ok) ok = hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+        if (e == hipSuccess && !ev) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     };
     for (int k = 0; k < lbm_ctx::GS; k++) {
         mk(c->ev_fork[k]);
@@ -664,7 +671,8 @@ bool create_step_events(lbm_ctx *c) {
             mk(c->ev_P[k][g]);
         }
     }
-    return ok;
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking);
+    return e;
 }
 
 void destroy_step_events(lbm_ctx *c) {
@@ -692,6 +700,7 @@ constexpr int GRAPH_STEPS = 2;
 
 int build_graph(lbm_ctx *c, int from) {
     hipGraph_t graph;
+    if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t e1 = hipSuccess;
     for (int k = 0; k < GRAPH_STEPS && e1 == hipSuccess; k++)
@@ -830,22 +839,6 @@ int lbm_create(const lbm_config *cfg, void *workspace, size_t ws_bytes, void *hi
     c->ev_used = 0;
     for (int k = 0; k < LBM_NPHASES; k++) { c->phase_ms[k] = 0.0; c->phase_n[k] = 0; }
     c->err[0] = 0;
-    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) {
-        delete c;
-        return fail(nullptr, LBM_E_HIP, "hipStreamCreateWithFlags failed");
-    }
-    if (hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking) != hipSuccess) {
-        (void)hipStreamDestroy(c->cap_stream);
-        delete c;
-        return fail(nullptr, LBM_E_HIP, "hipStreamCreateWithFlags failed");
-    }
-    if (!create_step_events(c)) {
-        destroy_step_events(c);
-        (void)hipStreamDestroy(c->side_stream);
-        (void)hipStreamDestroy(c->cap_stream);
-        delete c;
-        return fail(nullptr, LBM_E_HIP, "hipEventCreateWithFlags failed");
-    }
     // beta(eps) (Eq. 2) and (1 - beta)/tau for every possible clamped count
     std::vector<double> beta(L.Smax + 1), arel(L.Smax + 1);
     const double tau = cfg->tau;
@@ -860,6 +853,7 @@ int lbm_create(const lbm_config *cfg, void *workspace, size_t ws_bytes, void *hi
     chk(hipMemcpyAsync(wsp<double>(c, L.off_arel), arel.data(), arel.size() * 8, hipMemcpyHostToDevice, c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_nown), 0u, (int64_t)((L.N + 7) / 8 * 2), c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_flags), 0u, 16, c->stream));
+    chk(launch_fill_u32(wsp<uint32_t>(c, L.off_arrived), 0u, FORCE_PARTS, c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_qr), 0u,
                         (int64_t)L.N * (int64_t)((cfg->storage == LBM_FP64 ? sizeof(QRec) : sizeof(QRec32)) / 4),
                         c->stream));
@@ -876,9 +870,6 @@ int lbm_create(const lbm_config *cfg, void *workspace, size_t ws_bytes, void *hi
     }
     chk(hipStreamSynchronize(c->stream));
     if (r != LBM_OK) {
-        destroy_step_events(c);
-        (void)hipStreamDestroy(c->side_stream);
-        (void)hipStreamDestroy(c->cap_stream);
         delete c;
         return r;  // message already in the thread's last error
     }
@@ -894,10 +885,10 @@ void lbm_destroy(lbm_ctx *c) {
         (void)hipEventDestroy(e.a);
         (void)hipEventDestroy(e.b);
     }
-    (void)hipStreamSynchronize(c->side_stream);
+    if (c->side_stream) (void)hipStreamSynchronize(c->side_stream);
     destroy_step_events(c);
-    (void)hipStreamDestroy(c->side_stream);
-    (void)hipStreamDestroy(c->cap_stream);
+    if (c->side_stream) (void)hipStreamDestroy(c->side_stream);
+    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
 }
 
@@ -1150,6 +1141,7 @@ int lbm_step(lbm_ctx *c, int64_t nsteps) {
         return fail(c, LBM_E_STATE, "lbm_step before lbm_set_particles (n may be 0) or lbm_load");
     if (nsteps == 0) return LBM_OK;
     hipError_t e;
+    if (c->np > 0 && !one_stream(c)) HIPCHK(c, need_side_stream(c));
     HIPCHK(c, prepare_cells(c));
     constexpr int GS = lbm_ctx::GS;
     // steps queued one by one (timing mode, or the steps beyond whole graphs)
@@ -1247,7 +1239,7 @@ int lbm_set_neighbour_list(lbm_ctx *c, int every, double skin) {
     if (every > 0 && !(skin > 0.0 && skin <= 2.0 * c->L.rmax))
         return fail(c, LBM_E_INVALID, "skin must be in (0, 2 max_radius]");
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->side_stream));
+    if (c->side_stream) HIPCHK(c, hipStreamSynchronize(c->side_stream));
     const int old_every = c->nl_every;
     const double old_skin = c->nl_skin;
     c->nl_every = every;
@@ -1271,7 +1263,7 @@ int lbm_get_neighbour_list(lbm_ctx *c, int *every, double *skin, int64_t *builds
     if (every) *every = c->nl_every;
     if (skin) *skin = c->nl_skin;
     if (builds) {
-        HIPCHK(c, hipStreamSynchronize(c->side_stream));
+        if (c->side_stream) HIPCHK(c, hipStreamSynchronize(c->side_stream));
         HIPCHK(c, hipMemcpy(builds, c->ws + c->L.off_nl_state + 8, 8, hipMemcpyDeviceToHost));
     }
     return LBM_OK;
