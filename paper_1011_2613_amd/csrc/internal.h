@@ -73,7 +73,7 @@ struct Particles {
 constexpr int FOOT_SEG_MAX = 256;
 constexpr int FOOT_SEG_UNITS = 4096;
 int foot_segments(int D, int np, double rmax);
-constexpr int FORCE_PARTS = 1024;  // workgroups of all particles that share particles, at most
+constexpr int FORCE_PARTS = 256;  // workgroups of all particles that share particles, at most
 
 // Entries between the starts of two segments of particle p's list: its
 // bounding box's items split evenly.

@@ -1407,7 +1407,10 @@ static void force_nt(const ForceArgs &a, dim3 g, hipStream_t s) {
 // 64 per sphere on many particles (1 166 400 discs: 1.18 against 1.62 ms with 64
 // lanes each; spheres within 3 % with 16 or 32), four times as many while that
 // leaves fewer than four wavefronts per SIMD and a thread still has an entry;
-// beyond 256, several workgroups per particle, an entry per thread.  With few
+// beyond 256, several workgroups per particle, an entry per thread, 256 in all
+// (each one's agent-scope release and arrival cost more than the shorter walk
+// saves beyond that: 16 spheres R = 10, us with 1 / 4 / 16 / 64 workgroups each:
+// 49 / 21 / 17 / 33, 64 spheres with 1 / 4 / 16: 32 / 20 / 47).  With few
 // particles the walk over the list bounds the step: one sphere R = 16 10.4 us
 // with 64 workgroups against 46 with 1 024 threads and 240 with 64, 310 spheres R = 5.3 11 us
 // with 256 against 18 with 64, 16 discs R = 6 8.1 us with 64 against 10.7 with 16.
