@@ -38,14 +38,6 @@ __device__ __forceinline__ double disp_periodic(double d, double L) {
     return d > 0.5 * L ? dm : (d < -0.5 * L ? dp : d);
 }
 
-// Displacement node coordinate - particle coordinate along axis a.
-__device__ __forceinline__ double node_disp(const Geom &g, int axis, int coord, double xp) {
-    const double d = (double)coord - xp;
-    if (axis == 0) return disp_periodic(d, g.Lx);
-    if (axis == 1) return g.wall_y ? d : disp_periodic(d, g.Ly);
-    return disp_periodic(d, g.Lz);
-}
-
 // Sorts up to 4 owner records ascending (missing entries are 0xffffffff).
 __device__ __forceinline__ void sort4(uint32_t &a, uint32_t &b, uint32_t &c, uint32_t &d) {
 #define LBIMB_CSWAP(p, q) { uint32_t lo_ = min(p, q), hi_ = max(p, q); p = lo_; q = hi_; }
@@ -56,12 +48,17 @@ __device__ __forceinline__ void sort4(uint32_t &a, uint32_t &b, uint32_t &c, uin
 // Solid velocity V_S at node (x,y,z): count-weighted mean of the owners'
 // rigid-body velocities v_p + omega_p x (x_n - x_p), owners in ascending id;
 // also the total sub-sample count and the node's beta and (1 - beta)/tau from
-// the tables.  Memory is read in three dependent rounds at most: the owner
-// records (all at once), the two table entries together with the first
-// owner's nine particle values, and one round per further owner.
-template <class L>
+// the table.  R is the type of the velocities: binary64, or binary32 for
+// half-precision storage, whose collision is binary32 (the displacement is
+// formed in binary64 and rounded once, table entries are rounded; holding no
+// binary64 temporaries keeps that kernel at six wavefronts per SIMD).  Memory
+// is read in three dependent rounds at most: the owner records (all at once),
+// the table entry together with the first owner's record, and one round per
+// further owner.
+template <class L, class R>
 __device__ __forceinline__ int solid_velocity(const LBArgs &a, int64_t n, int nown, int x, int y,
-                                              int z, double V[3], double &beta, double &arel) {
+                                              int z, R V[3], R &beta, R &arel) {
+    constexpr bool F32 = sizeof(R) == 4;
     const int64_t N = a.g.N;
     const int k = nown < MAX_OWNERS ? nown : MAX_OWNERS;
     uint32_t r[4];
@@ -73,96 +70,61 @@ __device__ __forceinline__ int solid_velocity(const LBArgs &a, int64_t n, int no
     for (int j = 0; j < MAX_OWNERS; j++)
         if (j < k) total += (int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
     const int cc = total < a.Smax ? total : a.Smax;
-    beta = a.beta_tab[cc];
-    arel = a.arel_tab[cc];
-    double num[3] = {0.0, 0.0, 0.0};
-    const int P = a.np;
+    const double2 ba = ((const double2 *)a.tab)[cc];
+    beta = (R)ba.x;
+    arel = (R)ba.y;
+    R num[3] = {R(0), R(0), R(0)};
 #pragma unroll
     for (int j = 0; j < MAX_OWNERS; j++) {
         if (j < k) {
-            const int p = (int)(r[j] >> SLOT_COUNT_BITS);
-            const int cnt = (int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
-            const double X0 = a.px[p], X1 = a.px[P + p], X2 = L::D == 3 ? a.px[2 * P + p] : 0.0;
-            const double U0 = a.pv[p], U1 = a.pv[P + p], U2 = L::D == 3 ? a.pv[2 * P + p] : 0.0;
-            const double W0 = L::D == 3 ? a.pw[p] : 0.0, W1 = L::D == 3 ? a.pw[P + p] : 0.0;
-            const double W2 = a.pw[2 * P + p];
-            const double rx = node_disp(a.g, 0, x, X0);
-            const double ry = node_disp(a.g, 1, y, X1);
-            double vr[3];
-            if (L::D == 3) {
-                const double rz = node_disp(a.g, 2, z, X2);
-                vr[0] = U0 + (W1 * rz - W2 * ry);
-                vr[1] = U1 + (W2 * rx - W0 * rz);
-                vr[2] = U2 + (W0 * ry - W1 * rx);
+            const PRec *rec = a.rec + (r[j] >> SLOT_COUNT_BITS);
+            const R c = (R)(int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
+            double X[3];
+            R U[3], W[3];
+            const double2 x01 = ((const double2 *)rec)[0];
+            X[0] = x01.x;
+            X[1] = x01.y;
+            if (F32) {
+                const double2 x2v = ((const double2 *)rec)[1];  // x_z, v_x, v_y
+                const float4 vw = ((const float4 *)rec)[2];     // v_z, omega
+                X[2] = x2v.x;
+                U[0] = (R)__builtin_bit_cast(float, __double2loint(x2v.y));
+                U[1] = (R)__builtin_bit_cast(float, __double2hiint(x2v.y));
+                U[2] = (R)vw.x;
+                W[0] = (R)vw.y;
+                W[1] = (R)vw.z;
+                W[2] = (R)vw.w;
             } else {
-                vr[0] = U0 - W2 * ry;
-                vr[1] = U1 + W2 * rx;
-                vr[2] = 0.0;
+                X[2] = L::D == 3 ? rec->x[2] : 0.0;
+                const double2 v01 = ((const double2 *)rec)[3], v2w = ((const double2 *)rec)[4],
+                              w12 = ((const double2 *)rec)[5];
+                U[0] = (R)v01.x;
+                U[1] = (R)v01.y;
+                U[2] = (R)v2w.x;
+                W[0] = (R)v2w.y;
+                W[1] = (R)w12.x;
+                W[2] = (R)w12.y;
             }
-            const double c = (double)cnt;
+            const R rx = (R)disp_periodic((double)x - X[0], a.Ld[0]);
+            const R ry = (R)disp_periodic((double)y - X[1], a.Ld[1]);
+            R vr[3];
+            if (L::D == 3) {
+                const R rz = (R)disp_periodic((double)z - X[2], a.Ld[2]);
+                vr[0] = U[0] + (W[1] * rz - W[2] * ry);
+                vr[1] = U[1] + (W[2] * rx - W[0] * rz);
+                vr[2] = U[2] + (W[0] * ry - W[1] * rx);
+            } else {
+                vr[0] = U[0] - W[2] * ry;
+                vr[1] = U[1] + W[2] * rx;
+                vr[2] = R(0);
+            }
 #pragma unroll
             for (int d = 0; d < L::D; d++) num[d] = num[d] + c * vr[d];
         }
     }
-    const double den = (double)total;
+    const R den = (R)total;
 #pragma unroll
-    for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : 0.0;
-    return total;
-}
-
-// The same in binary32 (half-precision storage path, whose collision is
-// binary32): the node - centre displacement is formed in binary64 and rounded
-// once, the rigid-body velocities and their count-weighted mean are binary32,
-// beta and (1 - beta)/tau are the binary64 table entries rounded.  Holding no
-// binary64 temporaries keeps that kernel at six wavefronts per SIMD.
-template <class L>
-__device__ __forceinline__ int solid_velocity_f32(const LBArgs &a, int64_t n, int nown, int x, int y,
-                                                  int z, float V[3], float &beta, float &arel) {
-    const int64_t N = a.g.N;
-    const int k = nown < MAX_OWNERS ? nown : MAX_OWNERS;
-    uint32_t r[4];
-#pragma unroll
-    for (int j = 0; j < MAX_OWNERS; j++) r[j] = j < k ? a.slots[(int64_t)j * N + n] : 0xffffffffu;
-    sort4(r[0], r[1], r[2], r[3]);
-    int total = 0;
-#pragma unroll
-    for (int j = 0; j < MAX_OWNERS; j++)
-        if (j < k) total += (int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
-    const int cc = total < a.Smax ? total : a.Smax;
-    beta = (float)a.beta_tab[cc];
-    arel = (float)a.arel_tab[cc];
-    float num[3] = {0.0f, 0.0f, 0.0f};
-    const int P = a.np;
-#pragma unroll
-    for (int j = 0; j < MAX_OWNERS; j++) {
-        if (j < k) {
-            const int p = (int)(r[j] >> SLOT_COUNT_BITS);
-            const int cnt = (int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
-            const float rx = (float)node_disp(a.g, 0, x, a.px[p]);
-            const float ry = (float)node_disp(a.g, 1, y, a.px[P + p]);
-            const float U0 = (float)a.pv[p], U1 = (float)a.pv[P + p];
-            const float U2 = L::D == 3 ? (float)a.pv[2 * P + p] : 0.0f;
-            const float W0 = L::D == 3 ? (float)a.pw[p] : 0.0f, W1 = L::D == 3 ? (float)a.pw[P + p] : 0.0f;
-            const float W2 = (float)a.pw[2 * P + p];
-            float vr[3];
-            if (L::D == 3) {
-                const float rz = (float)node_disp(a.g, 2, z, a.px[2 * P + p]);
-                vr[0] = U0 + (W1 * rz - W2 * ry);
-                vr[1] = U1 + (W2 * rx - W0 * rz);
-                vr[2] = U2 + (W0 * ry - W1 * rx);
-            } else {
-                vr[0] = U0 - W2 * ry;
-                vr[1] = U1 + W2 * rx;
-                vr[2] = 0.0f;
-            }
-            const float c = (float)cnt;
-#pragma unroll
-            for (int d = 0; d < L::D; d++) num[d] = num[d] + c * vr[d];
-        }
-    }
-    const float den = (float)total;
-#pragma unroll
-    for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : 0.0f;
+    for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : R(0);
     return total;
 }
 
@@ -271,7 +233,7 @@ __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, 
     double V[3] = {0.0, 0.0, 0.0};
     int total = 0;
     double beta = 0.0, ar = a.arel0;
-    if (nown != 0) total = solid_velocity<L>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
+    if (nown != 0) total = solid_velocity<L, double>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
     double VV = V[0] * V[0] + V[1] * V[1];
     if (L::D == 3) VV = VV + V[2] * V[2];
     Eq64<L> eqV = eq;
@@ -326,10 +288,10 @@ __device__ __forceinline__ void collide_shifted(const LBArgs &a, uint64_t n, int
             // half-precision storage: binary32 V_S (six wavefronts per SIMD
             // instead of five, measured faster); binary32 storage keeps the
             // binary64 V_S (measured faster there)
-            total = solid_velocity_f32<L>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
+            total = solid_velocity<L, float>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
         } else {
             double Vd[3], bd, ad;
-            total = solid_velocity<L>(a, (int64_t)n, nown, x, y, z, Vd, bd, ad);
+            total = solid_velocity<L, double>(a, (int64_t)n, nown, x, y, z, Vd, bd, ad);
             for (int d = 0; d < 3; d++) V[d] = (float)Vd[d];
             beta = (float)bd;
             ar = (float)ad;

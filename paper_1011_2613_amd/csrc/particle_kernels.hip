@@ -45,6 +45,20 @@ __device__ __forceinline__ void bbox(const Particles &P, int p, int D, int lo[3]
     }
 }
 
+// The lattice kernel's record of particle p, one value per thread t < 9.
+__device__ __forceinline__ void write_rec(const Particles &P, int p, int t) {
+    if (t >= 9) return;
+    const double *src = t < 3 ? P.x : (t < 6 ? P.v : P.w);
+    const double val = src[(t % 3) * P.np + p];
+    PRec &r = P.rec[p];
+    if (t < 3) {
+        r.x[t] = val;
+    } else {
+        (t < 6 ? r.vf : r.wf)[t % 3] = (float)val;
+        (t < 6 ? r.v : r.w)[t % 3] = val;
+    }
+}
+
 // Number of sub-cell samples of a node inside a particle: offsets
 // (k + 1/2)/S - 1/2 per axis from the node, inside test dx^2 + dy^2 (+ dz^2)
 // <= R^2 evaluated left to right, d0/d1/d2 the node-minus-centre displacement.
@@ -201,6 +215,7 @@ __device__ __forceinline__ void foot_one(const FootArgs &a, int p) {
     const int P = a.P.np;
     int lo[3], hi[3];
     bbox(a.P, p, D, lo, hi);
+    write_rec(a.P, p, (int)threadIdx.x);
     if (threadIdx.x == 0)
         for (int d = 0; d < 3; d++) {
             a.P.bb[d * P + p] = lo[d];
@@ -614,6 +629,7 @@ __device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootL
     const int q = live ? p : 0;  // the lanes of a missing particle run every loop empty
     int lo[3], hi[3];
     bbox(a.P, q, D, lo, hi);
+    if (live && s == 0) write_rec(a.P, p, sub);
     if (live && sub == 0 && s == 0)
         for (int d = 0; d < 3; d++) {
             a.P.bb[d * P + p] = lo[d];

@@ -34,8 +34,8 @@ struct Layout {
     int64_t N;
     int P;
     int64_t cell_budget;
-    size_t off_fA, off_fB, off_nown, off_slots, off_qr, off_beta, off_arel;
-    size_t off_x, off_v, off_w, off_R, off_m, off_I, off_fixed, off_Fh, off_Th, off_Fc, off_bb;
+    size_t off_fA, off_fB, off_nown, off_slots, off_qr, off_beta;
+    size_t off_x, off_v, off_w, off_R, off_m, off_I, off_fixed, off_Fh, off_Th, off_Fc, off_rec, off_bb;
     size_t off_list, off_list_len;
     int list_cap;
     double rmax;
@@ -83,8 +83,7 @@ Layout make_layout(const lbm_config *c) {
     L.off_nown = take(((size_t)L.N + 7) / 8 * 8);
     L.off_slots = take((size_t)MAX_OWNERS * L.N * 4);
     L.off_qr = take((size_t)L.N * (c->storage == LBM_FP64 ? sizeof(QRec) : sizeof(QRec32)));
-    L.off_beta = take((size_t)(L.Smax + 1) * 8);
-    L.off_arel = take((size_t)(L.Smax + 1) * 8);
+    L.off_beta = take((size_t)(L.Smax + 1) * 16);  // beta and (1 - beta) / tau, interleaved
     const size_t P = (size_t)L.P;
     L.off_x = take(3 * P * 8);
     L.off_v = take(3 * P * 8);
@@ -96,6 +95,7 @@ Layout make_layout(const lbm_config *c) {
     L.off_Fh = take(3 * P * 8);
     L.off_Th = take(3 * P * 8);
     L.off_Fc = take(3 * P * 8);
+    L.off_rec = take(P * sizeof(PRec));
     // footprint records of two steps (the current and the last completed
     // one: the slab pipeline paints the next footprint before a step ends):
     // bounding boxes, lists of every node of the bounding box of the largest
@@ -219,6 +219,7 @@ Particles particles(lbm_ctx *c, int buf) {
     P.Fh = wsp<double>(c, c->L.off_Fh);
     P.Th = wsp<double>(c, c->L.off_Th);
     P.Fc = wsp<double>(c, c->L.off_Fc);
+    P.rec = wsp<PRec>(c, c->L.off_rec);
     P.bb = wsp<int>(c, c->L.off_bb + fb);
     P.list = wsp<uint32_t>(c, c->L.off_list + fb);
     P.list_len = wsp<int>(c, c->L.off_list_len + fb);
@@ -445,13 +446,12 @@ LBArgs lb_args(lbm_ctx *c, int from) {
     a.B = state(c, 1 - from);
     a.nown = wsp<uint8_t>(c, c->L.off_nown);
     a.slots = wsp<uint32_t>(c, c->L.off_slots);
-    a.beta_tab = wsp<double>(c, c->L.off_beta);
-    a.arel_tab = wsp<double>(c, c->L.off_arel);
+    a.tab = wsp<double>(c, c->L.off_beta);
     a.qr = wsp<char>(c, c->L.off_qr);
-    a.px = wsp<double>(c, c->L.off_x);
-    a.pv = wsp<double>(c, c->L.off_v);
-    a.pw = wsp<double>(c, c->L.off_w);
-    a.np = c->np;
+    a.rec = wsp<PRec>(c, c->L.off_rec);
+    a.Ld[0] = c->g.Lx;
+    a.Ld[1] = c->g.wall_y ? HUGE_VAL : c->g.Ly;
+    a.Ld[2] = c->g.Lz;
     a.g = c->g;
     a.Smax = c->L.Smax;
     a.arel0 = c->arel0;
@@ -840,17 +840,16 @@ int lbm_create(const lbm_config *cfg, void *workspace, size_t ws_bytes, void *hi
     for (int k = 0; k < LBM_NPHASES; k++) { c->phase_ms[k] = 0.0; c->phase_n[k] = 0; }
     c->err[0] = 0;
     // beta(eps) (Eq. 2) and (1 - beta)/tau for every possible clamped count
-    std::vector<double> beta(L.Smax + 1), arel(L.Smax + 1);
+    std::vector<double> tab(2 * (L.Smax + 1));
     const double tau = cfg->tau;
     for (int k = 0; k <= L.Smax; k++) {
         const double eps = (double)k / (double)L.Smax;
-        beta[k] = eps * (tau - 0.5) / ((1.0 - eps) + (tau - 0.5));
-        arel[k] = (1.0 - beta[k]) / tau;
+        tab[2 * k] = eps * (tau - 0.5) / ((1.0 - eps) + (tau - 0.5));
+        tab[2 * k + 1] = (1.0 - tab[2 * k]) / tau;
     }
     int r = LBM_OK;
     auto chk = [&](hipError_t e) { if (e != hipSuccess && r == LBM_OK) r = fail(c, LBM_E_HIP, "%s", hipGetErrorString(e)); };
-    chk(hipMemcpyAsync(wsp<double>(c, L.off_beta), beta.data(), beta.size() * 8, hipMemcpyHostToDevice, c->stream));
-    chk(hipMemcpyAsync(wsp<double>(c, L.off_arel), arel.data(), arel.size() * 8, hipMemcpyHostToDevice, c->stream));
+    chk(hipMemcpyAsync(wsp<double>(c, L.off_beta), tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_nown), 0u, (int64_t)((L.N + 7) / 8 * 2), c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_flags), 0u, 16, c->stream));
     chk(launch_fill_u32(wsp<uint32_t>(c, L.off_arrived), 0u, FORCE_PARTS, c->stream));
