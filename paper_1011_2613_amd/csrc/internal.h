@@ -208,6 +208,12 @@ struct ForceArgs {
     int file;              // 1: file the particle in the next step's cell list too
     int nc[3];             // cells per axis
     int *cell_old, *cell_new, *cell_ids;  // counts of this and the next step's list
+    // neighbour-list mode with file set: the guard of the next step (0: no lists)
+    int every;
+    double skin;
+    const double *xb;      // [3][P] positions at the last build
+    int *nl_flag, *nl_next, *nl_age;  // rebuild flags of this and the next step, age of the lists
+    int64_t *nl_builds;
     uint32_t *flags;
     Groups G;              // G.K > 1: the integration also files the particle in its next group
 };
@@ -229,7 +235,8 @@ struct CellArgs {
     int *nl;               // [P][NL_CAP] neighbour ids, ascending
     int *nl_len;           // [P]
     double *xb;            // [3][P] positions at the last build
-    int *nl_state;         // [0] rebuild flag, [1] steps since the last build
+    int *nl_flag;          // this step rebuilds the lists
+    int *nl_age;           // steps since the last build; INT_MAX: no lists yet
     int64_t *nl_builds;    // builds so far
     int64_t ncell;         // ncx * ncy * ncz
 };
@@ -347,8 +354,9 @@ hipError_t launch_stats(int lattice, int storage, const StatsArgs &a, hipStream_
 
 // launchers (particle_kernels.hip)
 hipError_t launch_foot_paint(const FootArgs &a, int D, hipStream_t s);
-// footprints and the contacts of the step from its cell list, in one launch
-// (plain step, sampled eps)
+// footprints and the contacts of the step from its cell list or neighbour
+// lists, in one launch (plain step, sampled eps)
+bool many_discs(int D, int np);  // discs take a thread each for the contacts
 hipError_t launch_foot_dem(const FootArgs &a, const CellArgs &c, int D, hipStream_t s);
 hipError_t launch_force(const ForceArgs &a, hipStream_t s);
 // files every particle in its group of the current step (G.nlist / G.ncount
@@ -360,6 +368,7 @@ hipError_t launch_dem(const CellArgs &a, hipStream_t s);
 // neighbour-list mode: the guard, a conditional rebuild (cells and lists) and
 // the contacts from the lists; phase_mid is called between the rebuild and the
 // contacts (for the per-phase timing)
+hipError_t launch_nl_check(const CellArgs &a, hipStream_t s);  // the guard alone
 hipError_t launch_nl_rebuild(const CellArgs &a, hipStream_t s);
 hipError_t launch_nl_contacts(const CellArgs &a, hipStream_t s);
 

@@ -577,6 +577,87 @@ __device__ __forceinline__ void dem_thread(const CellArgs &a, int i, int (*list)
     for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
 }
 
+// True when j lies within R_i + R_j + skin of i (minimum image).
+__device__ __forceinline__ bool nl_candidate(const CellArgs &a, int i, int j) {
+    const int P = a.P.np;
+    double d2 = 0.0;
+    for (int ax = 0; ax < a.D; ax++) {
+        double dd = a.P.x[ax * P + i] - a.P.x[ax * P + j];
+        if (!(ax == 1 && a.g.wall_y)) dd = pdisp(dd, ax == 0 ? a.g.Lx : (ax == 1 ? a.g.Ly : a.g.Lz));
+        d2 = d2 + dd * dd;
+    }
+    const double lim = (a.P.R[i] + a.P.R[j]) + a.skin;
+    return d2 < lim * lim;
+}
+
+// Contacts of particle i from its neighbour list by one wavefront, a lane per
+// listed neighbour; on a rebuild step the list is made first, from the cells
+// (edge >= 2 R_max + skin), and the build positions are recorded.  The touching
+// neighbours are summed in ascending id, as in dem_wave.  Cells, flag and lists
+// of other particles are not written here, so every wavefront decides alone.
+__device__ __forceinline__ void dem_list_wave(const CellArgs &a, int i, int *list, int *nl) {
+    const int lane = threadIdx.x & 63;
+    const int P = a.P.np;
+    const int D = a.D;
+    int n = 0, j = -1;
+    if (*a.nl_flag) {
+        if (lane == 0) *nl = 0;
+        lane_sync();
+        const int c0 = cell_coord(a, 0, a.P.x[i]);
+        const int c1 = cell_coord(a, 1, a.P.x[P + i]);
+        const int c2 = D == 3 ? cell_coord(a, 2, a.P.x[2 * P + i]) : 0;
+        int ox[3], oy[3], oz[3];
+        const int nxc = axis_cells(c0, a.ncx, true, ox);
+        const int nyc = axis_cells(c1, a.ncy, !a.g.wall_y, oy);
+        int nzc = 1;
+        oz[0] = 0;
+        if (D == 3) nzc = axis_cells(c2, a.ncz, true, oz);
+        if (lane < nxc * nyc * nzc) {
+            const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
+            const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
+            const int cnt = min(a.cell_count[c], CELL_CAP);
+            for (int s = 0; s < cnt; s++) {
+                const int q = a.cell_ids[c * CELL_CAP + s];
+                if (q == i || !nl_candidate(a, i, q)) continue;
+                const int slot = atomicAdd(nl, 1);
+                if (slot < NL_CAP) list[slot] = q;
+                else atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
+            }
+        }
+        lane_sync();
+        n = min(*nl, NL_CAP);
+        // each lane finds the place of its entry (ids differ)
+        const int mine = lane < n ? list[lane] : 0x7fffffff;
+        int place = 0;
+        for (int s = 0; s < n; s++) place += list[s] < mine ? 1 : 0;
+        lane_sync();
+        if (lane < n) list[place] = mine;
+        lane_sync();
+        if (lane < n) {
+            j = list[lane];
+            a.nl[(int64_t)i * NL_CAP + lane] = j;
+        }
+        if (lane == 0) a.nl_len[i] = n;
+        if (lane < D) a.xb[lane * P + i] = a.P.x[lane * P + i];
+    } else {
+        n = a.nl_len[i];
+        if (lane < n) {
+            j = a.nl[(int64_t)i * NL_CAP + lane];
+            list[lane] = j;
+        }
+        lane_sync();
+    }
+    static_assert(NL_CAP <= 64, "a lane per listed neighbour");
+    uint64_t touching = __ballot(j >= 0 && pair_force(a, i, j, nullptr));
+    if (lane == 0) {
+        if (__popcll(touching) > MAX_CONTACTS) atomicOr(a.flags, FLAG_CONTACT_OVERFLOW);
+        double F[3] = {0.0, 0.0, 0.0};
+        for (; touching; touching &= touching - 1) pair_force(a, i, list[__builtin_ctzll(touching)], F);
+        wall_force(a, i, F);
+        for (int d = 0; d < 3; d++) a.P.Fc[d * P + i] = F[d];
+    }
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) void k_dem_thread(CellArgs a) {
     __shared__ int list[MAX_CONTACTS][NT];
@@ -796,13 +877,14 @@ __device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootL
 template <int D, int S, int LPP, bool THREAD>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPP == 64 ? 5 : 4))) void k_foot(FootArgs a, CellArgs c, int ndem) {
     constexpr size_t FB = sizeof(FootLds<D, LPP>);
-    constexpr size_t DB = THREAD ? sizeof(int[MAX_CONTACTS][64]) : sizeof(int[MAX_CONTACTS + 1]);
+    constexpr size_t DB = THREAD ? sizeof(int[MAX_CONTACTS][64]) : sizeof(int[NL_CAP + 1]);
     __shared__ __attribute__((aligned(16))) char lds[FB > DB ? FB : DB];
     const int b = (int)blockIdx.x;
     if (b < ndem) {
         int *list = (int *)lds;
         if (THREAD) dem_thread<64>(c, b * 64 + (int)threadIdx.x, (int(*)[64])list);
-        else dem_wave(c, b, list, list + MAX_CONTACTS);
+        else if (c.every > 0) dem_list_wave(c, b, list, list + NL_CAP);
+        else dem_wave(c, b, list, list + NL_CAP);
         return;
     }
     foot_segment<D, S, LPP>(a, b - ndem, *(FootLds<D, LPP> *)lds);
@@ -1116,6 +1198,33 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
             a.cell_old[was + a.nc[0] * (w1 + a.nc[1] * w2)] = 0;
             file_in_cell(a.cell_new, a.cell_ids, a.flags, is + a.nc[0] * (i1 + a.nc[1] * i2), p);
         }
+        if (a.every > 0) {
+            // the guard of the neighbour lists for the next step: how far the
+            // particle has moved since the build (k_nl_check's sum), and the age
+            double dd = 0.0;
+            if (live && d < D) {
+                dd = xn - a.xb[d * P + p];
+                if (!(d == 1 && a.g.wall_y)) dd = pdisp(dd, d == 0 ? a.g.Lx : (d == 1 ? a.g.Ly : a.g.Lz));
+            }
+            double d2 = 0.0;
+            for (int ax = 0; ax < D; ax++) {
+                const double v = __shfl(dd, gbase + ax, 64);
+                d2 = d2 + v * v;
+            }
+            const double lim = 0.49 * a.skin;
+            if (live && sub == 0) {
+                bool again = !(d2 < lim * lim);
+                if (p == 0) {
+                    const int built = *a.nl_flag;
+                    const int age = built ? 1 : *a.nl_age + 1;
+                    *a.nl_age = age;
+                    if (built) *a.nl_builds = *a.nl_builds + 1;
+                    *a.nl_flag = 0;
+                    again = again || age >= a.every;
+                }
+                if (again) atomicOr(a.nl_next, 1);
+            }
+        }
     }
 }
 
@@ -1194,7 +1303,7 @@ __global__ void k_list_q(ForceArgs a, double *out) {
 __global__ void k_nl_check(CellArgs a) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const int P = a.P.np;
-    if (p == 0 && a.nl_state[1] >= a.every) atomicOr(&a.nl_state[0], 1);
+    if (p == 0 && *a.nl_age >= a.every) atomicOr(a.nl_flag, 1);
     if (p >= P) return;
     double d2 = 0.0;
     for (int ax = 0; ax < a.D; ax++) {
@@ -1203,12 +1312,12 @@ __global__ void k_nl_check(CellArgs a) {
         d2 = d2 + dd * dd;
     }
     const double lim = 0.49 * a.skin;
-    if (!(d2 < lim * lim)) atomicOr(&a.nl_state[0], 1);
+    if (!(d2 < lim * lim)) atomicOr(a.nl_flag, 1);
 }
 
 // Cell binning, on rebuild steps only (the counts are zero on entry).
 __global__ void k_nl_cells(CellArgs a) {
-    if (!a.nl_state[0]) return;
+    if (!*a.nl_flag) return;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const int P = a.P.np;
     if (p >= P) return;
@@ -1221,24 +1330,11 @@ __global__ void k_nl_cells(CellArgs a) {
     else atomicOr(a.flags, FLAG_CELL_OVERFLOW);
 }
 
-// True when j lies within R_i + R_j + skin of i (minimum image).
-__device__ __forceinline__ bool nl_candidate(const CellArgs &a, int i, int j) {
-    const int P = a.P.np;
-    double d2 = 0.0;
-    for (int ax = 0; ax < a.D; ax++) {
-        double dd = a.P.x[ax * P + i] - a.P.x[ax * P + j];
-        if (!(ax == 1 && a.g.wall_y)) dd = pdisp(dd, ax == 0 ? a.g.Lx : (ax == 1 ? a.g.Ly : a.g.Lz));
-        d2 = d2 + dd * dd;
-    }
-    const double lim = (a.P.R[i] + a.P.R[j]) + a.skin;
-    return d2 < lim * lim;
-}
-
 // List build, on rebuild steps only: one wavefront per particle, each lane
 // scans one neighbour cell (cell edge >= 2 R_max + skin), the candidates are
 // gathered in LDS and sorted by id; the build positions are recorded.
 __global__ __launch_bounds__(256) void k_nl_build(CellArgs a) {
-    if (!a.nl_state[0]) return;
+    if (!*a.nl_flag) return;
     __shared__ int list[4][NL_CAP];
     __shared__ int nlist[4];
     const int lane = threadIdx.x & 63;
@@ -1307,7 +1403,7 @@ __global__ void k_dem_list(CellArgs a) {
 
 // After a rebuild: clear the cell counts for the next one.
 __global__ void k_nl_clear(CellArgs a) {
-    if (!a.nl_state[0]) return;
+    if (!*a.nl_flag) return;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.ncell;
          c += (int64_t)gridDim.x * blockDim.x)
         a.cell_count[c] = 0;
@@ -1316,12 +1412,12 @@ __global__ void k_nl_clear(CellArgs a) {
 // Ages the lists and lowers the rebuild flag (one thread, after every other
 // kernel of the step's neighbour work has read the flag).
 __global__ void k_nl_finish(CellArgs a) {
-    if (a.nl_state[0]) {
-        a.nl_state[0] = 0;
-        a.nl_state[1] = 1;
+    if (*a.nl_flag) {
+        *a.nl_flag = 0;
+        *a.nl_age = 1;
         *a.nl_builds = *a.nl_builds + 1;
     } else {
-        a.nl_state[1] = a.nl_state[1] + 1;
+        *a.nl_age = *a.nl_age + 1;
     }
 }
 
@@ -1394,9 +1490,11 @@ int foot_segments(int D, int np, double rmax) {
     return nseg;
 }
 
+bool many_discs(int D, int np) { return D == 2 && np >= DISC_MANY; }
+
 static hipError_t paint_any(const FootArgs &a, const CellArgs &c, bool dem, int D, hipStream_t s) {
     if (D == 3) return paint_plain<3, 64, false>(a, c, dem, s);
-    return a.P.np >= DISC_MANY ? paint_plain<2, 16, true>(a, c, dem, s) : paint_plain<2, 64, false>(a, c, dem, s);
+    return many_discs(D, a.P.np) ? paint_plain<2, 16, true>(a, c, dem, s) : paint_plain<2, 64, false>(a, c, dem, s);
 }
 
 hipError_t launch_foot_paint(const FootArgs &a, int D, hipStream_t s) {
@@ -1490,10 +1588,15 @@ hipError_t launch_cells(const CellArgs &a, hipStream_t s) {
 
 hipError_t launch_dem(const CellArgs &a, hipStream_t s) {
     if (a.P.np == 0) return hipSuccess;
-    if (a.D == 2 && a.P.np >= DISC_MANY)
+    if (many_discs(a.D, a.P.np))
         hipLaunchKernelGGL(k_dem_thread<128>, dim3(blocks_for(a.P.np, 128)), dim3(128), 0, s, a);
     else
         hipLaunchKernelGGL(k_dem, dim3(blocks_for(a.P.np, 4)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_nl_check(const CellArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_nl_check, dim3(blocks_for(a.P.np, 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

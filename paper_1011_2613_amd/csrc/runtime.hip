@@ -266,6 +266,10 @@ bool particle_ok(const lbm_ctx *c, double r, const double *pos, const double *ve
     return true;
 }
 
+// Neighbour-list state: rebuild flag of the steps reading state A, age of the
+// lists, builds (64 bits), rebuild flag of the other steps.
+int *nl_flag(lbm_ctx *c, int which) { return wsp<int>(c, c->L.off_nl_state + (which == 0 ? 0 : 16)); }
+
 CellArgs cell_args(lbm_ctx *c, int which = 0) {
     CellArgs a;
     a.P = particles(c, c->cur);  // positions and velocities only
@@ -283,7 +287,8 @@ CellArgs cell_args(lbm_ctx *c, int which = 0) {
     a.nl = wsp<int>(c, c->L.off_nl);
     a.nl_len = wsp<int>(c, c->L.off_nl_len);
     a.xb = wsp<double>(c, c->L.off_xb);
-    a.nl_state = wsp<int>(c, c->L.off_nl_state);
+    a.nl_flag = nl_flag(c, which);
+    a.nl_age = wsp<int>(c, c->L.off_nl_state + 4);
     a.nl_builds = wsp<int64_t>(c, c->L.off_nl_state + 8);
     a.ncell = (int64_t)c->ncx * c->ncy * c->ncz;
     return a;
@@ -294,8 +299,9 @@ CellArgs cell_args(lbm_ctx *c, int which = 0) {
 // for it.
 hipError_t nl_reset(lbm_ctx *c) {
     c->cells_ready = false;
-    hipError_t e = launch_fill_u32(wsp<uint32_t>(c, c->L.off_nl_state), 0u, 4, c->stream);
-    if (e == hipSuccess) e = launch_fill_u32(wsp<uint32_t>(c, c->L.off_nl_state), 1u, 1, c->stream);
+    hipError_t e = launch_fill_u32(wsp<uint32_t>(c, c->L.off_nl_state), 0u, 5, c->stream);
+    // an age beyond every limit: the guard asks for a build
+    if (e == hipSuccess) e = launch_fill_u32(wsp<uint32_t>(c, c->L.off_nl_state + 4), 0x7fffffffu, 1, c->stream);
     if (e == hipSuccess)
         e = launch_fill_u32(wsp<uint32_t>(c, c->L.off_cc), 0u, (int64_t)c->ncx * c->ncy * c->ncz, c->stream);
     return e;
@@ -487,30 +493,55 @@ ForceArgs force_args(lbm_ctx *c, int buf, const Groups &G) {
     fo.cell_old = wsp<int>(c, buf == 0 ? c->L.off_cc : c->L.off_cc2);
     fo.cell_new = wsp<int>(c, buf == 0 ? c->L.off_cc2 : c->L.off_cc);
     fo.cell_ids = wsp<int>(c, c->L.off_cid);
+    fo.every = c->nl_every;
+    fo.skin = c->nl_skin;
+    fo.xb = wsp<double>(c, c->L.off_xb);
+    fo.nl_flag = nl_flag(c, buf);
+    fo.nl_next = nl_flag(c, 1 - buf);
+    fo.nl_age = wsp<int>(c, c->L.off_nl_state + 4);
+    fo.nl_builds = wsp<int64_t>(c, c->L.off_nl_state + 8);
     return fo;
 }
 
 // Whether the plain step runs as three launches on one stream: footprints with
 // the contacts, lattice, and the force sums, whose integration files each
 // particle in the next step's cell list (the counts alternate with the state,
-// so one array is filled while the other is cleared).  Neighbour lists, the
-// table lookup and the timing of every phase keep the cell list and the
-// contacts in launches of their own on the side stream.  Measured per step
-// against the two-stream schedule: 256 x 256 with 16 discs 22.4 against 36.7 us,
-// one sphere in 80^3 87 against 100 us, 192 x 756 x 192 with 8 317 spheres 20 us
-// less (FP64 1.69 ms).
+// so one array is filled while the other is cleared) and, with neighbour lists,
+// runs the guard of the next step.  The table lookup, the timing of every phase
+// and neighbour lists of many discs (whose contacts take a thread each) keep
+// the cell list, the lists and the contacts in launches of their own on the
+// side stream.  Measured per step against the two-stream schedule: 256 x 256
+// with 16 discs 22.4 against 36.7 us, one sphere in 80^3 87 against 100 us,
+// 192 x 756 x 192 with 8 317 spheres 20 us less (FP64 1.69 ms); with neighbour
+// lists (six launches of their own) 101 x 163 x 77 with 310 spheres 72 against
+// 85 us.
 bool one_stream(const lbm_ctx *c) {
-    return c->nl_every == 0 && c->cfg.eps_mode == LBM_EPS_SAMPLING && c->timing != 1 && c->pipe_K == 1;
+    return c->cfg.eps_mode == LBM_EPS_SAMPLING && c->timing != 1 && c->pipe_K == 1 &&
+           !(c->nl_every > 0 && many_discs(c->L.D, c->np));
 }
 
-// The cell list of the coming step, where no step before it filed one.
+// The cell list and the guard's decision of the coming step, where no step
+// before it left them.
 hipError_t prepare_cells(lbm_ctx *c) {
     if (c->np == 0 || c->cells_ready || !one_stream(c)) return hipSuccess;
     hipError_t e = launch_fill_u32(wsp<uint32_t>(c, c->cur == 0 ? c->L.off_cc2 : c->L.off_cc), 0u,
                                    (int64_t)c->ncx * c->ncy * c->ncz, c->stream);
     if (e == hipSuccess) e = launch_cells(cell_args(c, c->cur), c->stream);
+    if (c->nl_every > 0) {
+        for (int k = 0; k < 2 && e == hipSuccess; k++) e = launch_fill_u32((uint32_t *)nl_flag(c, k), 0u, 1, c->stream);
+        if (e == hipSuccess) e = launch_nl_check(cell_args(c, c->cur), c->stream);
+    }
     c->cells_ready = e == hipSuccess;
     return e;
+}
+
+// Before a step that bins the particles itself: neighbour lists expect zero
+// counts in the first array, which the steps before may have filled.
+hipError_t drop_cells(lbm_ctx *c, hipStream_t s) {
+    const bool filled = c->cells_ready;
+    c->cells_ready = false;
+    if (!filled || c->nl_every == 0) return hipSuccess;
+    return launch_fill_u32(wsp<uint32_t>(c, c->L.off_cc), 0u, (int64_t)c->ncx * c->ncy * c->ncz, s);
 }
 
 // Phase markers for the timing mode.
@@ -547,9 +578,9 @@ hipError_t enqueue_plain(lbm_ctx *c, int from, hipStream_t s, int slot) {
         const FootArgs fa = foot_args(c, from, groups_of(c, from, -1));
         if ((e = launch_foot_dem(fa, cell_args(c, from), c->L.D, s)) != hipSuccess) return e;
     } else if (c->np > 0) {
-        c->cells_ready = false;
         CellArgs ca = cell_args(c);
         hipStream_t d = c->side_stream;
+        if ((e = drop_cells(c, s)) != hipSuccess) return e;
         if ((e = hipEventRecord(c->ev_fork[slot], s)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(d, c->ev_fork[slot], 0)) != hipSuccess) return e;
         phase_begin(c, 3, d);
@@ -599,7 +630,7 @@ hipError_t enqueue_pipe(lbm_ctx *c, int from, hipStream_t s, int slot, bool firs
     const int prev = (slot + lbm_ctx::GS - 1) % lbm_ctx::GS;
     hipStream_t d = c->side_stream;
     const int lattice = c->cfg.lattice, storage = c->cfg.storage;
-    c->cells_ready = false;
+    if ((e = drop_cells(c, s)) != hipSuccess) return e;
     if (first) {
         if ((e = hipEventRecord(c->ev_fork[slot], s)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(d, c->ev_fork[slot], 0)) != hipSuccess) return e;
