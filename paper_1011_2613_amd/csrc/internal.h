@@ -143,6 +143,7 @@ struct LBArgs {
     const PRec *rec;       // [np] particle records, written with the footprint
     Geom g;
     double Ld[3];          // period of a displacement per axis; infinite across walls (no image)
+    double Lh[3];          // half of it
     int Smax;
     double arel0;          // 1 / tau
     double cg[19];         // c_i . g_fluid per direction

@@ -48,17 +48,16 @@ __device__ __forceinline__ void sort4(uint32_t &a, uint32_t &b, uint32_t &c, uin
 // Solid velocity V_S at node (x,y,z): count-weighted mean of the owners'
 // rigid-body velocities v_p + omega_p x (x_n - x_p), owners in ascending id;
 // also the total sub-sample count and the node's beta and (1 - beta)/tau from
-// the table.  R is the type of the velocities: binary64, or binary32 for
-// half-precision storage, whose collision is binary32 (the displacement is
-// formed in binary64 and rounded once, table entries are rounded; holding no
-// binary64 temporaries keeps that kernel at six wavefronts per SIMD).  Memory
-// is read in three dependent rounds at most: the owner records (all at once),
-// the table entry together with the first owner's record, and one round per
-// further owner.
-template <class L, class R>
+// the table.  Memory is read in three dependent rounds at most: the owner
+// records (all at once), the table entry together with the first owner's
+// particle record, and one round per further owner.  A particle record is five
+// 16-byte loads (three in binary32) where the separate arrays were nine
+// scattered ones: 192 x 756 x 192 with 8 317 spheres 1 547 -> 1 524 us in
+// binary64 storage and 484 -> 460 us in half precision, 8192 x 2048 with 21 361
+// discs 418 -> 412 us.
+template <class L>
 __device__ __forceinline__ int solid_velocity(const LBArgs &a, int64_t n, int nown, int x, int y,
-                                              int z, R V[3], R &beta, R &arel) {
-    constexpr bool F32 = sizeof(R) == 4;
+                                              int z, double V[3], double &beta, double &arel) {
     const int64_t N = a.g.N;
     const int k = nown < MAX_OWNERS ? nown : MAX_OWNERS;
     uint32_t r[4];
@@ -71,60 +70,119 @@ __device__ __forceinline__ int solid_velocity(const LBArgs &a, int64_t n, int no
         if (j < k) total += (int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
     const int cc = total < a.Smax ? total : a.Smax;
     const double2 ba = ((const double2 *)a.tab)[cc];
-    beta = (R)ba.x;
-    arel = (R)ba.y;
-    R num[3] = {R(0), R(0), R(0)};
+    beta = ba.x;
+    arel = ba.y;
+    double num[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < MAX_OWNERS; j++) {
         if (j < k) {
             const PRec *rec = a.rec + (r[j] >> SLOT_COUNT_BITS);
-            const R c = (R)(int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
-            double X[3];
-            R U[3], W[3];
-            const double2 x01 = ((const double2 *)rec)[0];
-            X[0] = x01.x;
-            X[1] = x01.y;
-            if (F32) {
-                const double2 x2v = ((const double2 *)rec)[1];  // x_z, v_x, v_y
-                const float4 vw = ((const float4 *)rec)[2];     // v_z, omega
-                X[2] = x2v.x;
-                U[0] = (R)__builtin_bit_cast(float, __double2loint(x2v.y));
-                U[1] = (R)__builtin_bit_cast(float, __double2hiint(x2v.y));
-                U[2] = (R)vw.x;
-                W[0] = (R)vw.y;
-                W[1] = (R)vw.z;
-                W[2] = (R)vw.w;
-            } else {
-                X[2] = L::D == 3 ? rec->x[2] : 0.0;
-                const double2 v01 = ((const double2 *)rec)[3], v2w = ((const double2 *)rec)[4],
-                              w12 = ((const double2 *)rec)[5];
-                U[0] = (R)v01.x;
-                U[1] = (R)v01.y;
-                U[2] = (R)v2w.x;
-                W[0] = (R)v2w.y;
-                W[1] = (R)w12.x;
-                W[2] = (R)w12.y;
-            }
-            const R rx = (R)disp_periodic((double)x - X[0], a.Ld[0]);
-            const R ry = (R)disp_periodic((double)y - X[1], a.Ld[1]);
-            R vr[3];
+            const double c = (double)(int)(r[j] & ((1u << SLOT_COUNT_BITS) - 1u));
+            const double2 x01 = ((const double2 *)rec)[0], v01 = ((const double2 *)rec)[3],
+                          v2w = ((const double2 *)rec)[4], w12 = ((const double2 *)rec)[5];
+            const double rx = disp_periodic((double)x - x01.x, a.Ld[0]);
+            const double ry = disp_periodic((double)y - x01.y, a.Ld[1]);
+            double vr[3];
             if (L::D == 3) {
-                const R rz = (R)disp_periodic((double)z - X[2], a.Ld[2]);
-                vr[0] = U[0] + (W[1] * rz - W[2] * ry);
-                vr[1] = U[1] + (W[2] * rx - W[0] * rz);
-                vr[2] = U[2] + (W[0] * ry - W[1] * rx);
+                const double rz = disp_periodic((double)z - rec->x[2], a.Ld[2]);
+                vr[0] = v01.x + (w12.x * rz - w12.y * ry);
+                vr[1] = v01.y + (w12.y * rx - v2w.y * rz);
+                vr[2] = v2w.x + (v2w.y * ry - w12.x * rx);
             } else {
-                vr[0] = U[0] - W[2] * ry;
-                vr[1] = U[1] + W[2] * rx;
-                vr[2] = R(0);
+                vr[0] = v01.x - w12.y * ry;
+                vr[1] = v01.y + w12.y * rx;
+                vr[2] = 0.0;
             }
 #pragma unroll
             for (int d = 0; d < L::D; d++) num[d] = num[d] + c * vr[d];
         }
     }
-    const R den = (R)total;
+    const double den = (double)total;
 #pragma unroll
-    for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : R(0);
+    for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : 0.0;
+    return total;
+}
+
+// The same for half-precision storage, whose collision is binary32: velocities
+// in binary32, the displacement formed in binary64 and rounded once, table
+// entries rounded.  That kernel is bound by vector-instruction issue as much as
+// by memory, so what most wavefronts do not need is behind a branch that the
+// wavefront takes as one: further owners and their sort, the minimum image,
+// and the division.  192 x 756 x 192 with 8 317 spheres: 460 -> 418 us.  (The
+// other two storage modes wait for memory; there the same branches cost 1 to
+// 2 %, 1 924 -> 1 949 us on 512 x 252 x 512 in binary32.)
+template <class L>
+__device__ __forceinline__ int solid_velocity32(const LBArgs &a, int64_t n, int nown, int x, int y,
+                                                int z, float V[3], float &beta, float &arel) {
+    constexpr uint32_t CMASK = (1u << SLOT_COUNT_BITS) - 1u;
+    const int64_t N = a.g.N;
+    const int k = nown < MAX_OWNERS ? nown : MAX_OWNERS;
+    uint32_t r[4] = {a.slots[n], 0xffffffffu, 0xffffffffu, 0xffffffffu};
+    int total = (int)(r[0] & CMASK);
+    if (__any(k > 1)) {  // a node with several owners in the wavefront
+#pragma unroll
+        for (int j = 1; j < MAX_OWNERS; j++)
+            if (j < k) {
+                r[j] = a.slots[(int64_t)j * N + n];
+                total += (int)(r[j] & CMASK);
+            }
+        sort4(r[0], r[1], r[2], r[3]);
+    }
+    const int cc = total < a.Smax ? total : a.Smax;
+    const double2 ba = ((const double2 *)a.tab)[cc];
+    beta = (float)ba.x;
+    arel = (float)ba.y;
+    float num[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int j = 0; j < MAX_OWNERS; j++) {
+        if (j == 0 || j < k) {
+            const PRec *rec = a.rec + (r[j] >> SLOT_COUNT_BITS);
+            const float c = (float)(int)(r[j] & CMASK);
+            const double2 x01 = ((const double2 *)rec)[0], x2v = ((const double2 *)rec)[1];  // x, v_x and v_y
+            const float4 vw = ((const float4 *)rec)[2];                                      // v_z, omega
+            const float v0 = __builtin_bit_cast(float, __double2loint(x2v.y));
+            const float v1 = __builtin_bit_cast(float, __double2hiint(x2v.y));
+            double dx = (double)x - x01.x, dy = (double)y - x01.y, dz = L::D == 3 ? (double)z - x2v.x : 0.0;
+            if (__any(fabs(dx) > a.Lh[0] || fabs(dy) > a.Lh[1] || (L::D == 3 && fabs(dz) > a.Lh[2]))) {
+                dx = dx > a.Lh[0] ? dx - a.Ld[0] : (dx < -a.Lh[0] ? dx + a.Ld[0] : dx);
+                dy = dy > a.Lh[1] ? dy - a.Ld[1] : (dy < -a.Lh[1] ? dy + a.Ld[1] : dy);
+                if (L::D == 3) dz = dz > a.Lh[2] ? dz - a.Ld[2] : (dz < -a.Lh[2] ? dz + a.Ld[2] : dz);
+            }
+            const float rx = (float)dx, ry = (float)dy, rz = (float)dz;
+            float vr[3];
+            if (L::D == 3) {
+                vr[0] = v0 + (vw.z * rz - vw.w * ry);
+                vr[1] = v1 + (vw.w * rx - vw.y * rz);
+                vr[2] = vw.x + (vw.y * ry - vw.z * rx);
+            } else {
+                vr[0] = v0 - vw.w * ry;
+                vr[1] = v1 + vw.w * rx;
+                vr[2] = 0.0f;
+            }
+#pragma unroll
+            for (int d = 0; d < L::D; d++) num[d] = num[d] + c * vr[d];
+        }
+    }
+    const float den = (float)total;
+    // num / den by the reciprocal of den and one correction: the correctly
+    // rounded quotient for every num away from under- and overflow and every
+    // whole den up to 4096, above four counts of ten bits (checked for all
+    // 2^23 significands), in three instructions instead of ten.  A wavefront
+    // with a zero or another num outside the range divides.
+    const float n2 = L::D == 3 ? num[2] : num[0];
+    const float lo = fminf(fminf(fabsf(num[0]), fabsf(num[1])), fabsf(n2));
+    const float hi = fmaxf(fmaxf(fabsf(num[0]), fabsf(num[1])), fabsf(n2));
+    if (__any(!(lo >= 0x1p-100f && hi <= 0x1p100f))) {
+#pragma unroll
+        for (int d = 0; d < 3; d++) V[d] = d < L::D ? num[d] / den : 0.0f;
+    } else {
+        const float inv = 1.0f / den;
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            const float q = num[d] * inv;
+            V[d] = d < L::D ? fmaf(fmaf(-q, den, num[d]), inv, q) : 0.0f;
+        }
+    }
     return total;
 }
 
@@ -233,7 +291,7 @@ __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, 
     double V[3] = {0.0, 0.0, 0.0};
     int total = 0;
     double beta = 0.0, ar = a.arel0;
-    if (nown != 0) total = solid_velocity<L, double>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
+    if (nown != 0) total = solid_velocity<L>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
     double VV = V[0] * V[0] + V[1] * V[1];
     if (L::D == 3) VV = VV + V[2] * V[2];
     Eq64<L> eqV = eq;
@@ -285,13 +343,13 @@ __device__ __forceinline__ void collide_shifted(const LBArgs &a, uint64_t n, int
     if (!wave_fluid && nown != 0) {
         if (nown > MAX_OWNERS) atomicOr(a.flags, FLAG_SLOT_OVERFLOW);
         if (ST == 2) {
-            // half-precision storage: binary32 V_S (six wavefronts per SIMD
-            // instead of five, measured faster); binary32 storage keeps the
-            // binary64 V_S (measured faster there)
-            total = solid_velocity<L, float>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
+            // half-precision storage: binary32 V_S (seven wavefronts per SIMD
+            // instead of five); binary32 storage keeps the binary64 V_S
+            // (measured faster there)
+            total = solid_velocity32<L>(a, (int64_t)n, nown, x, y, z, V, beta, ar);
         } else {
             double Vd[3], bd, ad;
-            total = solid_velocity<L, double>(a, (int64_t)n, nown, x, y, z, Vd, bd, ad);
+            total = solid_velocity<L>(a, (int64_t)n, nown, x, y, z, Vd, bd, ad);
             for (int d = 0; d < 3; d++) V[d] = (float)Vd[d];
             beta = (float)bd;
             ar = (float)ad;

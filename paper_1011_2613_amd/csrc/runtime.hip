@@ -458,6 +458,7 @@ LBArgs lb_args(lbm_ctx *c, int from) {
     a.Ld[0] = c->g.Lx;
     a.Ld[1] = c->g.wall_y ? HUGE_VAL : c->g.Ly;
     a.Ld[2] = c->g.Lz;
+    for (int d = 0; d < 3; d++) a.Lh[d] = 0.5 * a.Ld[d];
     a.g = c->g;
     a.Smax = c->L.Smax;
     a.arel0 = c->arel0;
