@@ -363,6 +363,15 @@ hipError_t launch_force(const ForceArgs &a, hipStream_t s);
 // files every particle in its group of the current step (G.nlist / G.ncount
 // must be cleared first)
 hipError_t launch_assign_groups(const ForceArgs &a, hipStream_t s);
+// reads by the host: the error flags (4 words), particles p0 .. p0 + n - 1 of
+// nvec vectors [3][np] as [n][3] each; dst may be pinned host memory
+struct ReadArgs {
+    const double *src[3];
+    double *dst[3];
+    int np;
+};
+hipError_t launch_read_flags(const uint32_t *flags, uint32_t *dst, hipStream_t s);
+hipError_t launch_read_vecs(const ReadArgs &a, int nvec, int p0, int n, hipStream_t s);
 hipError_t launch_list_q(const ForceArgs &a, double *out, hipStream_t s);
 hipError_t launch_cells(const CellArgs &a, hipStream_t s);
 hipError_t launch_dem(const CellArgs &a, hipStream_t s);

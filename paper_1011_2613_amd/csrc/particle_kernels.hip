@@ -1570,6 +1570,26 @@ hipError_t launch_assign_groups(const ForceArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+__global__ void k_read_flags(const uint32_t *flags, uint32_t *dst) {
+    if (threadIdx.x < 4) dst[threadIdx.x] = flags[threadIdx.x];
+}
+
+hipError_t launch_read_flags(const uint32_t *flags, uint32_t *dst, hipStream_t s) {
+    hipLaunchKernelGGL(k_read_flags, dim3(1), dim3(64), 0, s, flags, dst);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_read_vecs(ReadArgs a, int p0, int n) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x), v = (int)blockIdx.y;
+    if (i >= 3 * n) return;
+    a.dst[v][i] = a.src[v][(int64_t)(i % 3) * a.np + p0 + i / 3];
+}
+
+hipError_t launch_read_vecs(const ReadArgs &a, int nvec, int p0, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_read_vecs, dim3(blocks_for(3 * (int64_t)n, 256), (unsigned)nvec), dim3(256), 0, s, a, p0, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_list_q(const ForceArgs &a, double *out, hipStream_t s) {
     hipError_t e = launch_fill_u64((uint64_t *)out, 0ull, (int64_t)a.D * a.g.N, s);
     if (e != hipSuccess || a.P.np == 0) return e;
