@@ -31,7 +31,8 @@ __device__ __forceinline__ uint32_t belem(int Lb, int i, int x, int row) {
     return ((uint32_t)row * 19u + (uint32_t)i) * (uint32_t)Lb + (uint32_t)x;
 }
 
-// One tile of one box for one step.
+// One tile of one box for one step; NT: stores with the non-temporal hint.
+template <bool NT>
 __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchBox &bx, int tile, int parity) {
     using L = D3Q19;
     const int Lb = bx.L;
@@ -64,7 +65,10 @@ __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchBox &b
         const int cc = cnt < a.Smax ? cnt : a.Smax;
         const float beta = cnt != 0 ? beta_t[cc] : 0.0f;
         const float ar = cnt != 0 ? arel_t[cc] : bx.arel0f;
-        auto put = [&](int i, float v) { __builtin_nontemporal_store(v, &B[belem(Lb, i, x, row)]); };
+        auto put = [&](int i, float v) {
+            if (NT) __builtin_nontemporal_store(v, &B[belem(Lb, i, x, row)]);
+            else B[belem(Lb, i, x, row)] = v;
+        };
         float mom[3];
         shifted_node<L, false>(gg, wave_fluid, beta, ar, 0.0f, 0.0f, 0.0f, bx.cgf, put, mom);
         if (cnt != 0) {
@@ -76,12 +80,13 @@ __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchBox &b
     }
 }
 
+template <bool NT>
 __global__ __launch_bounds__(256) void k_batch_step(BatchArgs a, int parity) {
     const int t = blockIdx.x;
     const int b = a.tile_box[t];
     const BatchBox bx = a.boxes[b];
     if (!bx.active) return;
-    batch_tile(a, bx, t - bx.tile0, parity);
+    batch_tile<NT>(a, bx, t - bx.tile0, parity);
 }
 
 __global__ __launch_bounds__(256) void k_batch_persistent(BatchArgs a, int nsteps, int parity0) {
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(256) void k_batch_persistent(BatchArgs a, int nstep
                 __syncthreads();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
-            batch_tile(a, bx, t - bx.tile0, (parity0 + s) & 1);
+            batch_tile<true>(a, bx, t - bx.tile0, (parity0 + s) & 1);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
@@ -524,7 +529,9 @@ int batch_persistent_grid() {
 }
 
 hipError_t launch_batch_step(const BatchArgs &a, int parity, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_step, dim3((unsigned)a.ntiles), dim3(256), 0, s, a, parity);
+    const dim3 g((unsigned)a.ntiles), b(256);
+    if (through_caches(2.0 * 19.0 * 4.0 * (double)a.total_nodes)) hipLaunchKernelGGL(k_batch_step<false>, g, b, 0, s, a, parity);
+    else hipLaunchKernelGGL(k_batch_step<true>, g, b, 0, s, a, parity);
     return hipGetLastError();
 }
 

@@ -316,6 +316,20 @@ struct BatchArgs {
     double *F, *T;             // [nsph][3]
 };
 
+// Whether populations are loaded and stored through the caches or with the
+// non-temporal hint, by the bytes of both state arrays.  Up to the 32 MB of the
+// L2s together the hint leaves them to the reads; up to the 256 MB Infinity Cache
+// and a little beyond, a store without it is what the next step reads there;
+// above, the hint again.  Measured without particles, us per step with the hint
+// / without: D3Q19 binary64 26 MB 9.8 / 12.4, 43 MB 12.7 / 12.6, 66 MB 16.0 /
+// 14.2, 156 MB 29.7 / 27.3, 237 MB 48.7 / 39.9, 269 MB 47.3 / 44.6, 342 MB 62.8 /
+// 63.4, 638 MB 107 / 114; binary32 27 MB 10.0 / 10.2, 157 MB 33.6 / 30.0, 290 MB
+// 56.4 / 54.8, 382 MB 69.9 / 70.5; half precision 20 MB 9.1 / 9.8, 227 MB 49.6 /
+// 41.4; D2Q9 38 MB 10.6 / 11.7, 52 MB 13.7 / 13.0, 243 MB 51.3 / 43.0, 369 MB
+// 62.3 / 67.5; batched boxes of edge 48 34 MB 10.3 / 10.3, 134 MB 30.8 / 26.0,
+// 269 MB 54.3 / 54.2, 403 MB 77.0 / 89.4.
+inline bool through_caches(double state_bytes) { return state_bytes >= 48e6 && state_bytes <= 280e6; }
+
 // launchers (batch.hip)
 hipError_t launch_batch_step(const BatchArgs &a, int parity, hipStream_t s);
 hipError_t launch_batch_persistent(const BatchArgs &a, int nsteps, int parity0, int grid, hipStream_t s);

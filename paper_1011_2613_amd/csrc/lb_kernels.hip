@@ -206,7 +206,7 @@ __device__ __forceinline__ T *lane(T *row, uint32_t xbytes) {
 // threads of a block share y and z (the grid is one block row per lattice row),
 // so the bounce-back test and every source row base are uniform per block
 // (scalar registers); a lane adds its x, x - 1 or x + 1 (wrapped) byte offset.
-template <class L, class T>
+template <class L, class T, bool NTL = true>
 __device__ __forceinline__ void gather(const T *__restrict__ A, const Geom &g, int x, int y, int z,
                                        T (&f)[L::Q]) {
     const int nx = g.nx, ny = g.ny, nz = g.nz;
@@ -233,7 +233,8 @@ __device__ __forceinline__ void gather(const T *__restrict__ A, const Geom &g, i
                           : lane(A + row_elem(g, L::Q, i, sy, szz), xo);
         // binary64 populations are read with the non-temporal hint (measured
         // faster for the 8-byte pull on gfx950; no gain for the narrower types)
-        f[i] = sizeof(T) == 8 ? __builtin_nontemporal_load(src) : *src;
+        // unless the state stays in the Infinity Cache
+        f[i] = NTL && sizeof(T) == 8 ? __builtin_nontemporal_load(src) : *src;
     }
 }
 
@@ -251,7 +252,14 @@ struct Eq64 {
     }
 };
 
-template <class L>
+// A population store, past the caches (NT) or through them.
+template <bool NT, class T>
+__device__ __forceinline__ void put_pop(T v, T *dst) {
+    if (NT) __builtin_nontemporal_store(v, dst);
+    else *dst = v;
+}
+
+template <class L, bool NT>
 __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, int y, int z,
                                             const double (&f)[L::Q], int nown) {
     double rho = f[0];
@@ -283,7 +291,7 @@ __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, 
 #pragma unroll
         for (int i = 0; i < L::Q; i++) {
             const double out = f[i] - ar * (f[i] - eq(i)) + w3r[L::wc[i]] * a.cg[i];
-            __builtin_nontemporal_store(out, lane(Brow + (uint64_t)i * a.g.nx, xb));
+            put_pop<NT>(out, lane(Brow + (uint64_t)i * a.g.nx, xb));
         }
         return;
     }
@@ -305,7 +313,7 @@ __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, 
         const int o = L::opp[i];
         const double Om = (f[o] - f[i]) + (eqV(i) - eq(o));
         const double out = f[i] - ar * (f[i] - eq(i)) + beta * Om + w3r[L::wc[i]] * a.cg[i];
-        __builtin_nontemporal_store(out, lane(Brow + (uint64_t)i * a.g.nx, xb));
+        put_pop<NT>(out, lane(Brow + (uint64_t)i * a.g.nx, xb));
         if (L::cx[i] > 0) mx = mx + Om; else if (L::cx[i] < 0) mx = mx - Om;
         if (L::cy[i] > 0) my = my + Om; else if (L::cy[i] < 0) my = my - Om;
         if (L::D == 3) { if (L::cz[i] > 0) mz = mz + Om; else if (L::cz[i] < 0) mz = mz - Om; }
@@ -327,14 +335,14 @@ __device__ __forceinline__ void collide_f64(const LBArgs &a, uint64_t n, int x, 
 // g^eq_i = w_i (drho + rho (3 cu + 4.5 cu^2 - 1.5 u^2)); the solid operator
 // keeps its exact form because the w_i terms cancel:
 // Omega_i = (g_-i - g_i) + w_i rho [(3 cV + 4.5 cV^2 - 1.5 V^2) - (-3 cu + 4.5 cu^2 - 1.5 u^2)].
-template <class L, int ST>
+template <class L, int ST, bool NT>
 __device__ __forceinline__ void collide_shifted(const LBArgs &a, uint64_t n, int x, int y, int z,
                                                 const float (&gg)[L::Q], int nown) {
     using T = typename Store<ST>::T;
     T *const Brow = (T *)a.B + row_elem(a.g, L::Q, 0, y, z);
     const uint32_t xb = (uint32_t)x * (uint32_t)sizeof(T);
     auto put = [&](int i, float v) {
-        __builtin_nontemporal_store((T)v, lane(Brow + (uint64_t)i * a.g.nx, xb));
+        put_pop<NT>((T)v, lane(Brow + (uint64_t)i * a.g.nx, xb));
     };
     const bool wave_fluid = !__any(nown != 0);
     float beta = 0.0f, ar = a.arel0f;
@@ -393,7 +401,7 @@ __device__ __forceinline__ void tile_of(uint32_t &xt, int &y, int &z) {
     z = (int)(row / gridDim.y);
 }
 
-template <class L, int ST, bool XO>
+template <class L, int ST, bool XO, bool NT>
 __global__ __launch_bounds__(256) void k_lb(LBArgs a) {
     uint32_t xt;
     int y, z;
@@ -407,19 +415,19 @@ __global__ __launch_bounds__(256) void k_lb(LBArgs a) {
     // covered node can start its owner-record reads while they arrive
     const int nown = a.nown[n];
     T f[L::Q];
-    gather<L, T>((const T *)a.A, a.g, x, y, z, f);
+    gather<L, T, NT>((const T *)a.A, a.g, x, y, z, f);
     if (ST == 0) {
         double fd[L::Q];
 #pragma unroll
         for (int i = 0; i < L::Q; i++) fd[i] = (double)f[i];
-        collide_f64<L>(a, n, x, y, z, fd, nown);
+        collide_f64<L, NT>(a, n, x, y, z, fd, nown);
     } else {
         // FP32 storage holds g_i, FP16 storage g_i / w_i; the collision works
         // in the storage unit
         float gg[L::Q];
 #pragma unroll
         for (int i = 0; i < L::Q; i++) gg[i] = (float)f[i];
-        collide_shifted<L, ST>(a, n, x, y, z, gg, nown);
+        collide_shifted<L, ST, NT>(a, n, x, y, z, gg, nown);
     }
 }
 
@@ -542,10 +550,15 @@ static hipError_t lb_dispatch(const LBArgs &a, int width, int order, int cu_grou
     }
     const uint64_t groups = (uint64_t)grid.x * grid.y * grid.z;
     const unsigned lds = lds_reserve_bytes(cu_groups);
-    if (order == 1 && groups < ((uint64_t)1 << 32))
-        hipLaunchKernelGGL((k_lb<L, ST, true>), grid, dim3(block), lds, s, a);
-    else
-        hipLaunchKernelGGL((k_lb<L, ST, false>), grid, dim3(block), lds, s, a);
+    const bool xo = order == 1 && groups < ((uint64_t)1 << 32);
+    const dim3 b(block);
+    if (!through_caches(2.0 * L::Q * (double)a.g.N * sizeof(typename Store<ST>::T))) {
+        if (xo) hipLaunchKernelGGL((k_lb<L, ST, true, true>), grid, b, lds, s, a);
+        else hipLaunchKernelGGL((k_lb<L, ST, false, true>), grid, b, lds, s, a);
+    } else {
+        if (xo) hipLaunchKernelGGL((k_lb<L, ST, true, false>), grid, b, lds, s, a);
+        else hipLaunchKernelGGL((k_lb<L, ST, false, false>), grid, b, lds, s, a);
+    }
     return hipGetLastError();
 }
 
