@@ -186,7 +186,8 @@ int lbm_get_timing(lbm_ctx *ctx, double *ms, int64_t *launches);
 /* Launch shape of the lattice kernel (the update of Eq. 1 with the
  * immersed-boundary terms of Eq. 2).  threads: the workgroup width along x,
  * one workgroup covering all or part of one lattice row; 0 selects the
- * built-in rule (the whole row when nx <= 256, else 256 threads), otherwise
+ * built-in rule (the whole row when nx <= 256, else 256 threads, whose
+ * wavefronts may take 64-node stretches of different rows), otherwise
  * 64, 128, 192 or 256 (the end of a row that the last workgroup overhangs is
  * masked).  order: LBM_ORDER_LINEAR hands tiles to workgroups in launch
  * order; LBM_ORDER_XCD renumbers workgroups so that each of the GPU's 8

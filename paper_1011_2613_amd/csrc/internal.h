@@ -152,6 +152,7 @@ struct LBArgs {
     float tauf;
     uint32_t *flags;
     int y0, ny_run;        // rows y0 .. y0 + ny_run - 1 of every z plane (a slab; ny_run = ny: all)
+    int row_waves;         // > 0: a row's tiles of one wavefront, dealt to the wavefronts in turn (set by launch_lb)
 };
 
 // Slab pipeline (walls in y): the lattice update of a step runs slab by slab
