@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace lbimb {
@@ -68,6 +69,23 @@ struct Particles {
     int nseg;              // segments of each list: segment s starts at entry s list_seg()
     int np;
 };
+
+// Nodes of a footprint's bounding box along one axis, at most; the reserved
+// lists hold box_extent(R_max)^D entries.
+__host__ __device__ inline int box_extent(double R) { return (int)floor(2.0 * R + 1.0) + 1; }
+
+// Bounding box of a particle along one axis: the nodes whose cell may hold
+// samples of it, ceil(c - R - 1/2) .. floor(c + R + 1/2).  Both ends round by
+// themselves, so with R a rounding below a multiple of 1/2 they may both land on
+// a node and the box hold one node more than box_extent(R); the upper end then
+// stays out.  It lies R + 1/2 from the centre less a rounding, where no sample
+// (offsets of at most 1/2 - 1/(2S)) and no nonzero entry of the eps table is.
+__host__ __device__ inline void box_axis(double c, double R, int &lo, int &hi) {
+    const int ext = box_extent(R);
+    lo = (int)ceil(c - R - 0.5);
+    hi = (int)floor(c + R + 0.5);
+    if (hi - lo >= ext) hi = lo + ext - 1;
+}
 
 // Footprint segments per particle (foot_segments): at most FOOT_SEG_MAX, and
 // np nseg below FOOT_SEG_UNITS where there is more than one.

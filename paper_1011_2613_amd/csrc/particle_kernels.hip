@@ -33,15 +33,12 @@ __device__ __forceinline__ int wrapc(const Geom &g, int axis, int c) {
     return c < 0 ? c + n : c;
 }
 
-// Bounding box of nodes whose cell may hold samples of the particle:
-// ceil(x - R - 1/2) .. floor(x + R + 1/2) per axis.
+// Bounding box of nodes whose cell may hold samples of the particle (box_axis).
 __device__ __forceinline__ void bbox(const Particles &P, int p, int D, int lo[3], int hi[3]) {
     const double r = P.R[p];
     for (int a = 0; a < 3; a++) {
         if (a >= D) { lo[a] = hi[a] = 0; continue; }
-        const double c = P.x[a * P.np + p];
-        lo[a] = (int)ceil(c - r - 0.5);
-        hi[a] = (int)floor(c + r + 0.5);
+        box_axis(P.x[a * P.np + p], r, lo[a], hi[a]);
     }
 }
 
@@ -734,8 +731,8 @@ __device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootL
     const int i0 = s * seg, i1 = min(i0 + seg, items);
     const double r = a.P.R[q], R2 = r * r;
     const int64_t N = a.g.N;
-    const int cap = a.P.list_cap;
-    uint32_t *list = a.P.list + (int64_t)q * cap + i0;
+    const int room = a.P.list_cap - i0;  // places of the particle's list from the segment's start on
+    uint32_t *list = a.P.list + (int64_t)q * a.P.list_cap + i0;
     // (A) in binary32: the displacement of item (kx, ky, kz) from the centre
     // is base + k to 2e-5 at most (radii up to 62), so the bounds of the
     // squared distance over the cell's samples are good to 8e-3 at R = 62 and
@@ -815,6 +812,12 @@ __device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootL
             ncov += __popcll(m);
         }
         lane_sync();
+        // box_extent keeps a box within its list; were one longer, the run ends
+        // with the flag and nothing is written beyond the list
+        if (total + ncov > room) {
+            if (sub == 0) atomicOr(a.flags, FLAG_SLOT_OVERFLOW);
+            ncov = max(room - total, 0);
+        }
         // (C2) owner slots and list entries, UN rounds of claims in flight
         constexpr int UN = 2;
 #pragma unroll 1
@@ -1483,7 +1486,7 @@ static hipError_t paint_plain(const FootArgs &a, const CellArgs &c, bool dem, hi
 // Footprint segments per particle: with few particles a box is cut until
 // about 2 048 wavefronts are busy, down to 48 items per segment.
 int foot_segments(int D, int np, double rmax) {
-    const double ext = std::floor(2.0 * rmax + 1.0) + 1.0;
+    const double ext = (double)box_extent(rmax);
     const double items = D == 2 ? ext * ext : ext * ext * ext;
     int nseg = 1;
     while (nseg < FOOT_SEG_MAX && (int64_t)np * nseg < FOOT_SEG_UNITS / 2 && items >= 96.0 * nseg) nseg *= 2;

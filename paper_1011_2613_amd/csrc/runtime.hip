@@ -102,7 +102,7 @@ Layout make_layout(const lbm_config *c) {
     // bounding boxes, lists of every node of the bounding box of the largest
     // particle, list lengths; buffer k starts k * list_buf bytes after the first
     L.rmax = c->max_radius > 0.0 ? c->max_radius : 8.0;
-    const int ext = (int)std::floor(2.0 * L.rmax + 1.0) + 1;
+    const int ext = box_extent(L.rmax);
     L.list_cap = L.D == 2 ? ext * ext : ext * ext * ext;
     {
         const size_t o0 = o;
