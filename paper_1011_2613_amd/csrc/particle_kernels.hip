@@ -383,10 +383,21 @@ __device__ __forceinline__ int cell_coord(const CellArgs &a, int axis, double x)
     return cell_coord(a.g, axis == 0 ? a.ncx : (axis == 1 ? a.ncy : a.ncz), axis, x);
 }
 
-__device__ __forceinline__ void file_in_cell(int *cell_count, int *cell_ids, uint32_t *flags, int c, int p) {
+// Files particle p in cell c; beyond the cell's places it is only counted.
+// Who reads the cell for contacts or lists reports that (cell_entries): a list
+// filed ahead may never be read (the last step of a run, a step that keeps its
+// neighbour lists).
+__device__ __forceinline__ void file_in_cell(int *cell_count, int *cell_ids, int c, int p) {
     const int slot = atomicAdd(&cell_count[c], 1);
     if (slot < CELL_CAP) cell_ids[c * CELL_CAP + slot] = p;
-    else atomicOr(flags, FLAG_CELL_OVERFLOW);
+}
+
+// Particles listed in cell c.  Every particle's search includes its own cell,
+// so an overfull one is always seen.
+__device__ __forceinline__ int cell_entries(const CellArgs &a, int c) {
+    const int n = a.cell_count[c];
+    if (n > CELL_CAP) atomicOr(a.flags, FLAG_CELL_OVERFLOW);
+    return min(n, CELL_CAP);
 }
 
 __global__ void k_cells(CellArgs a) {
@@ -396,7 +407,7 @@ __global__ void k_cells(CellArgs a) {
     const int cx = cell_coord(a, 0, a.P.x[p]);
     const int cy = cell_coord(a, 1, a.P.x[P + p]);
     const int cz = a.D == 3 ? cell_coord(a, 2, a.P.x[2 * P + p]) : 0;
-    file_in_cell(a.cell_count, a.cell_ids, a.flags, cx + a.ncx * (cy + a.ncy * cz), p);
+    file_in_cell(a.cell_count, a.cell_ids, cx + a.ncx * (cy + a.ncy * cz), p);
 }
 
 // Neighbour cell offsets along one axis: {-1,0,1} wrapped (periodic, >= 3
@@ -486,7 +497,7 @@ __device__ __forceinline__ void dem_wave(const CellArgs &a, int i, int *list, in
         if (lane < nxc * nyc * nzc) {
             const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
             const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-            const int cnt = min(a.cell_count[c], CELL_CAP);
+            const int cnt = cell_entries(a, c);
             for (int s = 0; s < cnt; s++) {
                 const int j = a.cell_ids[c * CELL_CAP + s];
                 if (j == i) continue;
@@ -549,7 +560,7 @@ __device__ __forceinline__ void dem_thread(const CellArgs &a, int i, int (*list)
         for (int ky = 0; ky < nyc; ky++)
             for (int kx = 0; kx < nxc; kx++) {
                 const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-                const int cnt = min(a.cell_count[c], CELL_CAP);
+                const int cnt = cell_entries(a, c);
                 for (int s = 0; s < cnt; s++) {
                     const int j = a.cell_ids[c * CELL_CAP + s];
                     if (j == i) continue;
@@ -612,7 +623,7 @@ __device__ __forceinline__ void dem_list_wave(const CellArgs &a, int i, int *lis
         if (lane < nxc * nyc * nzc) {
             const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
             const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-            const int cnt = min(a.cell_count[c], CELL_CAP);
+            const int cnt = cell_entries(a, c);
             for (int s = 0; s < cnt; s++) {
                 const int q = a.cell_ids[c * CELL_CAP + s];
                 if (q == i || !nl_candidate(a, i, q)) continue;
@@ -1199,7 +1210,7 @@ __device__ __forceinline__ void force_unit(const ForceArgs &a, int p, int sub, b
         const int i1 = __shfl(is, gbase + 1, 64), i2 = __shfl(is, gbase + 2, 64);
         if (live && sub == 0) {
             a.cell_old[was + a.nc[0] * (w1 + a.nc[1] * w2)] = 0;
-            file_in_cell(a.cell_new, a.cell_ids, a.flags, is + a.nc[0] * (i1 + a.nc[1] * i2), p);
+            file_in_cell(a.cell_new, a.cell_ids, is + a.nc[0] * (i1 + a.nc[1] * i2), p);
         }
         if (a.every > 0) {
             // the guard of the neighbour lists for the next step: how far the
@@ -1327,10 +1338,7 @@ __global__ void k_nl_cells(CellArgs a) {
     const int cx = cell_coord(a, 0, a.P.x[p]);
     const int cy = cell_coord(a, 1, a.P.x[P + p]);
     const int cz = a.D == 3 ? cell_coord(a, 2, a.P.x[2 * P + p]) : 0;
-    const int c = cx + a.ncx * (cy + a.ncy * cz);
-    const int slot = atomicAdd(&a.cell_count[c], 1);
-    if (slot < CELL_CAP) a.cell_ids[c * CELL_CAP + slot] = p;
-    else atomicOr(a.flags, FLAG_CELL_OVERFLOW);
+    file_in_cell(a.cell_count, a.cell_ids, cx + a.ncx * (cy + a.ncy * cz), p);
 }
 
 // List build, on rebuild steps only: one wavefront per particle, each lane
@@ -1360,7 +1368,7 @@ __global__ __launch_bounds__(256) void k_nl_build(CellArgs a) {
         if (lane < nxc * nyc * nzc) {
             const int kx = lane % nxc, ky = (lane / nxc) % nyc, kz = lane / (nxc * nyc);
             const int c = ox[kx] + a.ncx * (oy[ky] + a.ncy * oz[kz]);
-            const int cnt = min(a.cell_count[c], CELL_CAP);
+            const int cnt = cell_entries(a, c);
             for (int s = 0; s < cnt; s++) {
                 const int j = a.cell_ids[c * CELL_CAP + s];
                 if (j == i || !nl_candidate(a, i, j)) continue;
