@@ -103,6 +103,15 @@ __device__ __forceinline__ int list_seg(const Particles &P, int p) {
     return (items + P.nseg - 1) / P.nseg;
 }
 
+// num / den from inv = 1 / den (correctly rounded): the product num inv and one
+// correction by the exact remainder, Markstein's method (P. Markstein, IBM J.
+// Res. Dev. 34, 1990).  The correctly rounded quotient for every whole den up to
+// 4096 and |num| in 2^-100 .. 2^100; the CPU tests check all significands.
+__host__ __device__ inline float quotient_whole(float num, float den, float inv) {
+    const float q = num * inv;
+    return fmaf(fmaf(-q, den, num), inv, q);
+}
+
 // Lattice geometry shared by every kernel.
 struct Geom {
     int nx, ny, nz;

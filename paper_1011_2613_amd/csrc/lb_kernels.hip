@@ -167,11 +167,9 @@ __device__ __forceinline__ int solid_velocity32(const LBArgs &a, int64_t n, int 
         }
     }
     const float den = (float)total;
-    // num / den by the reciprocal of den and one correction: the correctly
-    // rounded quotient for every num away from under- and overflow and every
-    // whole den up to 4096, above four counts of ten bits (checked for all
-    // 2^23 significands), in three instructions instead of ten.  A wavefront
-    // with a zero or another num outside the range divides.
+    // num / den by quotient_whole, in three instructions instead of ten; den is
+    // at most four counts of 512.  A wavefront with a zero or another num
+    // outside the range divides.
     const float n2 = L::D == 3 ? num[2] : num[0];
     const float lo = fminf(fminf(fabsf(num[0]), fabsf(num[1])), fabsf(n2));
     const float hi = fmaxf(fmaxf(fabsf(num[0]), fabsf(num[1])), fabsf(n2));
@@ -181,10 +179,7 @@ __device__ __forceinline__ int solid_velocity32(const LBArgs &a, int64_t n, int 
     } else {
         const float inv = 1.0f / den;
 #pragma unroll
-        for (int d = 0; d < 3; d++) {
-            const float q = num[d] * inv;
-            V[d] = d < L::D ? fmaf(fmaf(-q, den, num[d]), inv, q) : 0.0f;
-        }
+        for (int d = 0; d < 3; d++) V[d] = d < L::D ? quotient_whole(num[d], den, inv) : 0.0f;
     }
     return total;
 }
