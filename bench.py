@@ -405,6 +405,8 @@ def main():
         "roofline": base["roofline"],
         "roofline_step": base["roofline_step"],
         "phase_ms_per_step": base["phase_ms_per_step"],
+        "phase_schedule": "a pass of its own on two streams: cell list and contacts apart from the "
+                          "footprint and force launches that hold them in the timed steps",
         "variants": {v: {"value": round(r["mlups"], 1), "unit": "MLUPS", "dtype": DTYPE[v],
                          "ms_per_step": round(r["ms_per_step"], 4),
                          "roofline": r["roofline"], "roofline_step": r["roofline_step"],

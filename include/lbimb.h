@@ -177,8 +177,11 @@ int64_t lbm_particle_count(const lbm_ctx *ctx);
  * and returns the summed milliseconds and the number of launches of each phase
  * since timing was enabled.  Phases: 0 footprint, 1 lattice
  * (stream-collide-IMB), 2 hydrodynamic force and integration, 3 cell list,
- * 4 DEM contacts, 5 unused (integration runs inside phase 2).  Errors:
- * LBM_E_INVALID for another `enable`. */
+ * 4 DEM contacts, 5 unused (integration runs inside phase 2).  With 1 the cell
+ * list and the contacts are launches of their own on a second stream, beside
+ * the footprint and the lattice kernel, where a step otherwise has them in the
+ * force and footprint launches: the phases are not the split of an untimed
+ * step, and do not add up to one.  Errors: LBM_E_INVALID for another `enable`. */
 #define LBM_NPHASES 6
 int lbm_set_timing(lbm_ctx *ctx, int enable);
 int lbm_get_timing(lbm_ctx *ctx, double *ms, int64_t *launches);
@@ -254,7 +257,11 @@ int lbm_get_pipeline(const lbm_ctx *ctx, int *slabs);
  * twice, so the simulation advances by up to 48 (1 + steps) steps; the result
  * does not depend on the shape.  The lattice phase is timed as in timing
  * mode 2, and the candidate with the shortest mean lattice kernel time is
- * kept.  best_threads, best_order and best_cu_groups (each may be null)
+ * kept.  The 64-node stretches that the built-in rule deals out on some rows
+ * above 256 nodes are not among the candidates: on such rows the choice can be
+ * slower than width 0 in linear order without a cap, which
+ * lbm_set_lattice_block(ctx, 0, LBM_ORDER_LINEAR, 0) brings back.
+ * best_threads, best_order and best_cu_groups (each may be null)
  * receive it; ms_out (24 doubles, may be null) the mean milliseconds per
  * lattice launch of each candidate (the faster of the two passes; HUGE_VAL
  * for a skipped one).  The timing mode in force before the call is restored

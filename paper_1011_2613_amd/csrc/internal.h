@@ -417,10 +417,10 @@ hipError_t launch_read_vecs(const ReadArgs &a, int nvec, int p0, int n, hipStrea
 hipError_t launch_list_q(const ForceArgs &a, double *out, hipStream_t s);
 hipError_t launch_cells(const CellArgs &a, hipStream_t s);
 hipError_t launch_dem(const CellArgs &a, hipStream_t s);
-// neighbour-list mode: the guard, a conditional rebuild (cells and lists) and
-// the contacts from the lists; phase_mid is called between the rebuild and the
-// contacts (for the per-phase timing)
-hipError_t launch_nl_check(const CellArgs &a, hipStream_t s);  // the guard alone
+// neighbour-list mode: the guard alone; the guard, the binning and the list
+// build (each does nothing on a step that keeps its lists); the contacts from
+// the lists, then the clearing of the cell counts and the ageing
+hipError_t launch_nl_check(const CellArgs &a, hipStream_t s);
 hipError_t launch_nl_rebuild(const CellArgs &a, hipStream_t s);
 hipError_t launch_nl_contacts(const CellArgs &a, hipStream_t s);
 

@@ -555,6 +555,7 @@ static dim3 lattice_grid(const Geom &g, int &block) {
 // 256 x 192 1 027 / 530 / 333 -> 841 / 412 / 266, 400 x 128 x 128 (1 of 8) 393 /
 // 210 / 149 -> 350 / 179 / 130, 300 x 2 000 24.9 / 17.6 / 14.6 -> 21.8 / 15.2 /
 // 13.0; 700 x 700 (1 of 12) 18.2 / 13.1 / 11.2 -> 18.7 / 13.4 / 11.4, which stays.
+// A width that the caller or the autotuner sets keeps its stretches.
 static LBArgs flat_rows(LBArgs a, int width, int order, dim3 &grid) {
     a.row_waves = 0;
     const int waves = (a.g.nx + 63) / 64;

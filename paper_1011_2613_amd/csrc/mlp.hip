@@ -119,7 +119,8 @@ __device__ __forceinline__ void layer_tiles(const __bf16 *sin, const __bf16 *sw,
 // registers.  Bound by the SiLU's vector instructions (its exponential and
 // reciprocal issue at a quarter of the rate: about 300 issue cycles per row and
 // SIMD, 128 us at 1 048 576 rows) with the products' 36 us mostly beside them.
-// Measured at 1 048 576 rows with flags: 163 us (6.4 G rows/s) against 231 us
+// Measured at 1 048 576 rows with flags: 187 us (5.6 G rows/s; 185 us on inputs
+// that lie in the Infinity Cache, 188 us on inputs that do not) against 231 us
 // with one tile per wavefront and twelve wavefronts, and 561 us for a separate
 // pass over X for the flags.
 constexpr int FWD_WAVES = 8;

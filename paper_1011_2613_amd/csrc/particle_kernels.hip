@@ -885,7 +885,7 @@ __device__ __forceinline__ void foot_segment(const FootArgs &a, int block, FootL
 // (ndem workgroups; THREAD: one thread per particle, else one wavefront): both
 // read the particles only, and one launch keeps the step on one stream (a fork
 // to a second stream and back cost about 10 us each way in the step's chain).
-// Five wavefronts per SIMD (92 registers for spheres; 118 without the bound).
+// Five wavefronts per SIMD (96 registers for spheres; 118 without the bound).
 // 8 317 spheres: 62 us for both, where the footprint alone took 58 beside the
 // cell list and the contacts (63 us) on a second stream; 21 361 discs 38 us.
 template <int D, int S, int LPP, bool THREAD>
@@ -1440,11 +1440,14 @@ static unsigned blocks_for(int n, int per) { return (unsigned)((n + per - 1) / p
 constexpr int GROUP_GRID = 4096;
 
 // 2D runs of this many discs keep 16 lanes per disc in the footprint, four discs
-// per wavefront (1 166 400 discs: 1.96 against 2.75 ms with a wavefront each),
-// and a thread per disc for the contacts (21 361 discs 25 against 65 us,
-// 1 166 400 discs 0.54 against 4.4 ms).  With fewer, a wavefront or several per
-// disc shorten the chain (16 discs: footprint 5.4 against 22.6 us); 8 317
-// spheres with a thread each took 168 against 26 us.
+// per wavefront, and a thread per disc for the contacts; with fewer, a wavefront
+// or several per disc shorten the chain.  us per step with 16 lanes and a thread
+// / with a wavefront for both, R = 5 on a tenth of the area, FP64: 2 048 discs
+// 69.7 / 66.9, 4 096 105.6 / 105.0, 8 192 193.6 / 195.6, 12 000 283.0 / 283.3,
+// 16 384 361.5 / 364.1, 21 361 464 / 472, 40 000 910 / 927: within 1 % from
+// 4 096 to 16 384 discs, so the line lies where the contacts alone always gain
+// (1 166 400 discs 0.54 against 4.4 ms).  8 317 spheres with a thread each for
+// the contacts took 168 against 26 us.
 constexpr int DISC_MANY = 16384;
 
 template <int D, int NT, bool TAB>
